@@ -30,11 +30,13 @@ struct Layout {
   std::vector<int32_t> fwoff, fwjob;   // fusion job queues per XCD (CSR): job = rank << 8 | tile
   std::vector<int32_t> fcnt0;          // jobs of each queue handed out at launch
   int32_t nfwg = 0;                    // persistent fusion workgroups
+  std::vector<int32_t> frank;          // rank of each (layer, sequence, kv head) among the fusion units
+  int32_t njm = 1;                     // most jobs of a fusion unit
   std::vector<int64_t> toff, orow, drow;
   // workspace regions (byte offsets)
-  size_t off_plan, plan_bytes, off_qbf, off_part, off_S, off_gs, off_drop, total;
+  size_t off_plan, plan_bytes, off_qbf, off_part, off_S, off_gs, off_jstart, off_drop, total;
   // offsets inside the plan blob
-  size_t p_lp, p_nb, p_toff, p_kk, p_ns, p_orow, p_drow, p_funit, p_fwoff, p_fwjob, p_fcnt;
+  size_t p_lp, p_nb, p_toff, p_kk, p_ns, p_orow, p_drow, p_funit, p_fwoff, p_fwjob, p_fcnt, p_frank;
 };
 
 vc_status check_shape(const vc_shape *s) {
@@ -185,6 +187,10 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
       for (int32_t t = 0; t < nj; ++t) xj[x].push_back({cost, (int32_t)(rk << 8) | t});
       njobs += nj;
     }
+    y.frank.assign((size_t)y.h * y.B * y.Hkv, -1);
+    for (size_t rk = 0; rk < y.funit.size(); ++rk) y.frank[(size_t)y.funit[rk]] = (int32_t)rk;
+    y.njm = 1;
+    for (int32_t kk : y.k) y.njm = std::max(y.njm, (kk + kFuseRows - 1) / kFuseRows);
     y.fwoff.assign(kXcdsHost + 1, 0);
     y.fwjob.clear();
     y.fwjob.reserve((size_t)njobs);
@@ -223,6 +229,7 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
   y.p_fwoff = o; o += sizeof(int32_t) * y.fwoff.size();
   y.p_fcnt = o; o += sizeof(int32_t) * kXcdsHost;  // queue counters, reset by every plan upload
   y.p_fwjob = o; o += sizeof(int32_t) * y.fwjob.size();
+  y.p_frank = o; o += sizeof(int32_t) * y.frank.size();
   o = (o + 7) & ~size_t(7);
   y.plan_bytes = o;
 
@@ -235,6 +242,7 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
                               : sizeof(float2) * (size_t)units * y.nks * y.R));
   y.off_S = w; w = align_up(w + sizeof(float) * (size_t)y.Ls * y.Ntot * y.Hkv);
   y.off_gs = w; w = align_up(w + (y.mode == VC_RANK_GLOBAL ? sizeof(float) * (size_t)y.Ntot : 0));
+  y.off_jstart = w; w = align_up(w + sizeof(int32_t) * y.funit.size() * (size_t)y.njm);
   y.off_drop = w;
   for (int32_t l = 0; l < y.h; ++l) w = align_up(w + sizeof(int32_t) * (size_t)y.drow[(size_t)l * (y.B + 1) + y.B]);
   y.total = std::max<size_t>(w, kAlign);
@@ -407,6 +415,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   std::memcpy(blob.data() + y.p_fwoff, y.fwoff.data(), sizeof(int32_t) * y.fwoff.size());
   std::memcpy(blob.data() + y.p_fcnt, y.fcnt0.data(), sizeof(int32_t) * y.fcnt0.size());
   if (!y.fwjob.empty()) std::memcpy(blob.data() + y.p_fwjob, y.fwjob.data(), sizeof(int32_t) * y.fwjob.size());
+  if (!y.frank.empty()) std::memcpy(blob.data() + y.p_frank, y.frank.data(), sizeof(int32_t) * y.frank.size());
   {
     // Fusion unit records: absolute row addresses, so the fusion kernel
     // needs one dependent load before its index loads.
@@ -460,6 +469,9 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   pl.fwoff = reinterpret_cast<const int32_t *>(pb + y.p_fwoff);
   pl.fwjob = reinterpret_cast<const int32_t *>(pb + y.p_fwjob);
   pl.fcnt = reinterpret_cast<int32_t *>(pb + y.p_fcnt);
+  pl.frank = reinterpret_cast<const int32_t *>(pb + y.p_frank);
+  pl.jstart = reinterpret_cast<int32_t *>(ws + y.off_jstart);
+  pl.njm = y.njm;
   pl.qbf = reinterpret_cast<uint16_t *>(ws + y.off_qbf);
   pl.part = reinterpret_cast<float2 *>(ws + y.off_part);
   pl.pcol = reinterpret_cast<float *>(ws + y.off_part);

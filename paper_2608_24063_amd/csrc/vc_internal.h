@@ -74,6 +74,9 @@ struct PrunePlan {
   const FuseUnit *funit; // [nfunits] fusion units, most dropped rows first
   const int32_t *fwoff;  // [9] job queue offsets per XCD
   const int32_t *fwjob;  // fusion jobs: unit rank << 8 | 128-row tile, each queue longest first
+  const int32_t *frank;  // [h*B*Hkv] rank of a unit among the fusion units (-1: none)
+  int32_t *jstart;       // [nfunits][njm] dropped rows before a fusion job's first kept row (selection)
+  int32_t njm;           // most fusion jobs of a unit
   int32_t *fcnt;         // [8] jobs handed out per queue (reset by every plan upload)
   uint16_t *qbf;        // [Ls][B][Hq][W][d] window queries in bf16
   float2 *part;         // [U][nks][R] partial row statistics (max*sc, sum)

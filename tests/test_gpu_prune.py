@@ -243,6 +243,47 @@ def test_keep_all_returns_cache_unchanged(dev, orc, sg):
                 np.testing.assert_array_equal(vrows, sg.bf16_bits_to_f32(V))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("values", ["frames", "flat", "late"])
+def test_fusion_passes_over_far_tiles(dev, orc, d, values):
+    """Dropped tiles far below a row's running max are passed over, and the
+    tiles are walked from beside the job's first kept row.  Values in frames
+    (most tiles are far), nearly equal (none is), and in frames with a few
+    rows at the end of the sequence that tower over all others (the max rises
+    by far more than 2^32 after tiles have been passed over); dropped counts
+    around the half tile, the tile and the partial tile.  fp32 output: each
+    weight is a bf16 pair, within 2^-17 of itself, so a fused value is within
+    2^-17 (1 - mu) max|V_d| of the oracle's besides fp32 rounding."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    from synthgen.device import to_host_bf16
+    gen = np.random.default_rng(7)
+    params = vc.make_params(0.5, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, drop_all=True, v_out_fp32=True)
+    for n in (2, 62, 66, 128, 130, 256, 258, 700):
+        cent = gen.standard_normal((2, n // 16 + 1, d))
+        noise = gen.standard_normal((2, n, d))
+        V = 0.8 * cent[:, np.arange(n) // 16] + 0.6 * noise
+        if values == "flat":
+            V = 0.05 * noise
+        if values == "late":
+            V[:, -3:] = 30.0 * cent[:, :1]
+        Vt = [torch.from_numpy(v.astype(np.float32)).to(torch.bfloat16).to(dev) for v in V]
+        Kt = [torch.from_numpy(gen.standard_normal((n, d)).astype(np.float32)).to(torch.bfloat16).to(dev) for _ in V]
+        Qt = [torch.from_numpy(gen.standard_normal((1, 1, 4, d)).astype(np.float32)).to(dev) for _ in V]
+        pc = PruneCall(1, 2, 1, 1, d, 4, [n], params, Kt, Vt, Qt, with_drop=True)
+        pc.run()
+        torch.cuda.synchronize()
+        for l in range(2):
+            kept, drop = pc.idx_out[l].cpu().numpy(), pc.drop_out[l].cpu().numpy()
+            assert len(drop) == n - len(kept) and len(kept) == pc.k[l]
+            V16 = to_host_bf16(Vt[l])
+            ref = orc.fuse(V16, kept, drop, 1.0, 0.7)
+            got = pc.v_out[l].cpu().numpy().astype(np.float64)
+            big = np.abs(Vt[l].float().cpu().numpy()[drop]).max()
+            bound = 0.3 * 2.0 ** -17 * big + 4e-6 * np.abs(ref).max()
+            assert np.abs(got - ref).max() <= bound, (n, l, np.abs(got - ref).max(), bound)
+
+
 def test_mu_one_is_plain_pruning(dev, orc, sg):
     w = _custom(sg)
     r = Run(w, dev, mu=1.0, vfp32=True)
