@@ -95,12 +95,21 @@ __device__ __forceinline__ void unit_coords(const PrunePlan &p, int u, int &ls, 
 }
 
 // ---------------------------------------------------------------------------
-// Pass 1: row statistics.  Workgroup = (unit, 256-row query group, key split).
-// Wave w owns query rows qg*256 + w*64 + [0, 64) as MFMA B operands and all
-// four waves share each 64-key tile of K in LDS (A operands; direct loads into
-// a ring of three chunk-swizzled tiles, two ahead of the one in use), so the
-// product is Z^T (keys x queries): lane l sees query l%16 of each 16-row block
-// and keys 4*(l/16)+i, and keeps a running (max, sum) per query in registers.
+// Pass 1: row statistics.  Workgroup = (unit, at most 256 query rows, key
+// split).  A wave owns up to four 16-row blocks of queries as MFMA B operands
+// and all four waves share each 64-key tile of K in LDS (A operands; direct
+// loads into a ring of three chunk-swizzled tiles), so the product is Z^T
+// (keys x queries): lane l sees query l%16 of each 16-row block and keys
+// 4*(l/16)+i, and keeps a running (max, sum) per query in registers.
+//
+// The matrix and the vector unit bound it: per 16-row block and 64 keys, 16
+// matrix instructions and 16 (fma, exp, add) take 242 ns a SIMD in a probe of
+// this loop alone, of which the matrix instructions alone take 137.  Measured
+// on eight sequences of 14k to 23k tokens (448 rows a unit, 28 layers, 4 kv
+// heads, d = 128), with the other passes unchanged: products that run ahead
+// across tiles 1.61 -> 1.56 ms, rows dealt evenly over the SIMDs -> 1.51 ms
+// (1.60 without the alternation by SIMD).  Reading all keys from the caches
+// gains 3%; the workgroups' starts and ends take 0.08 ms.
 // ---------------------------------------------------------------------------
 // Softmax statistics of one 16-row query block (lane's row: qb*16 + l%16)
 // over the 64 keys of a tile.
@@ -141,38 +150,24 @@ __device__ __forceinline__ void stats_rows(f32x4 (&acc)[4], float &m, float &sum
   }
 }
 
-// One 64-key tile against the wave's four 16-row query blocks.  The K tile's
-// operands are read from LDS once; the matrix work of block qb+1 is issued
-// ahead of the softmax work of block qb so the two units overlap.
-template <int D, bool MASK>
-__device__ __forceinline__ void stats_tile(const uint16_t *kl, const bf16x8 (&bq)[4][D / 32],
-                                           float (&m)[4], float (&sum)[4], int tb, int k1, int lr,
-                                           int lg, float sc) {
-  constexpr int KS = D / 32;
-  bf16x8 a[4][KS];
+// A 64-key K tile's operands of one wave.
+template <int D>
+using KeyOps = bf16x8[4][D / 32];
+
+template <int D>
+__device__ __forceinline__ void key_operands(const uint16_t *kl, int lr, int lg, KeyOps<D> &a) {
 #pragma unroll
-  for (int kb = 0; kb < 4; ++kb)
+  for (int s = 0; s < D / 32; ++s)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) a[kb][s] = RowTileLds<D>::operand(kl, kb, s, lr, lg);
-  f32x4 cur[4], nxt[4];
+    for (int kb = 0; kb < 4; ++kb) a[kb][s] = RowTileLds<D>::operand(kl, kb, s, lr, lg);
+}
+// Products of the tile with one 16-row query block.
+template <int D>
+__device__ __forceinline__ void key_products(const KeyOps<D> &a, const bf16x8 (&bq)[D / 32], f32x4 (&acc)[4]) {
 #pragma unroll
-  for (int s = 0; s < KS; ++s)
+  for (int s = 0; s < D / 32; ++s)
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) cur[kb] = mfma_bf16(a[kb][s], bq[0][s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : cur[kb]);
-#pragma unroll
-  for (int qb = 0; qb < 4; ++qb) {
-    if (qb + 1 < 4) {
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-          nxt[kb] = mfma_bf16(a[kb][s], bq[qb + 1][s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : nxt[kb]);
-    }
-    stats_rows<MASK>(cur, m[qb], sum[qb], tb, k1, lg, sc);
-    if (qb + 1 < 4) interleave_mfma_valu<4 * KS, 4>();
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) cur[kb] = nxt[kb];
-  }
+    for (int kb = 0; kb < 4; ++kb) acc[kb] = mfma_bf16(a[kb][s], bq[s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[kb]);
 }
 
 // A 64-bit table entry of the plan chunk (two words, low first).
@@ -225,107 +220,189 @@ __global__ __launch_bounds__(256, 2) void k_score_stats(PrunePlan p, uint32_t *p
   const float *Q = reinterpret_cast<const float *>(chunk_u64(c, p.w_lp + 2 * (LP_Q * p.L + ls))) + qoff;
   uint16_t *Qb = p.qbf + (int64_t)ls * p.B * p.Hq * p.W * D + qoff;
 
-  // Query rows -> bf16 B operands (round to nearest even), zero past R.  All
-  // loads of a half (two 16-row blocks) are issued before any is used (rows
-  // clamped rather than branched on), so the prologue costs two round trips
-  // instead of one per load pair.
-  const int row0 = qg * kStatsRows + w * 64;
-  const bool active = row0 < p.R;  // wave-uniform: waves of padding rows only stage tiles
-  bf16x8 bq[4][KS];
-#pragma unroll
-  for (int hq = 0; hq < 2; ++hq) {
-    u32x4 raw[2][KS][2];
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int rc = min(row0 + (2 * hq + qq) * 16 + lr, p.R - 1);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const float *src = Q + (int64_t)rc * D + 32 * s + 8 * lg;
-        raw[qq][s][0] = ld16(src);
-        raw[qq][s][1] = ld16(src + 4);
-      }
-    }
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int qb = 2 * hq + qq;
-      const int row = row0 + qb * 16 + lr;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const u32x4 a = raw[qq][s][0], c = raw[qq][s][1];
-        u32x4 pk = {pack_bf16(__uint_as_float(a.x), __uint_as_float(a.y)),
-                    pack_bf16(__uint_as_float(a.z), __uint_as_float(a.w)),
-                    pack_bf16(__uint_as_float(c.x), __uint_as_float(c.y)),
-                    pack_bf16(__uint_as_float(c.z), __uint_as_float(c.w))};
-        if (row >= p.R) pk = u32x4{0, 0, 0, 0};
-        bq[qb][s] = as_bf16x8(pk);
-      }
-    }
-  }
-  // The first key split also leaves the bf16 queries for the column pass.
-  if (ks == 0) {
-#pragma unroll
-    for (int qb = 0; qb < 4; ++qb) {
-      const int row = row0 + qb * 16 + lr;
-      if (row < p.R) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) st16(Qb + (int64_t)row * D + 32 * s + 8 * lg, as_u32x4(bq[qb][s]));
-      }
-    }
-  }
-
-  float m[4], sum[4];
-#pragma unroll
-  for (int qb = 0; qb < 4; ++qb) { m[qb] = kFloor; sum[qb] = 0.f; }
+  // The unit's 16-row blocks are dealt evenly to its workgroups and to their
+  // waves.  Which waves of a workgroup take the extra blocks goes by the SIMD
+  // they run on and alternates with the workgroup's place on it, so that the
+  // SIMDs' loads come out even (448 rows: 7 blocks a SIMD, not 8 and 6).  A
+  // row's statistics do not depend on the wave that takes it.
+  __shared__ int s_slot, s_simd[4];
+  // hwreg(HW_ID, 0, 32): the wave's slot in bits 0-3, its SIMD in bits 4-5.
+  const uint32_t hw = __builtin_amdgcn_s_getreg(4 | (31 << 11));
+  if (tid == 0) s_slot = (int)(hw & 15u);
+  if (lane == 0) s_simd[w] = (int)((hw >> 4) & 3u);
+  __syncthreads();
+  const int slot = s_slot;
+  // (The four waves normally sit on four SIMDs; if not, each takes its own number.)
+  const bool four = ((1 << s_simd[0]) | (1 << s_simd[1]) | (1 << s_simd[2]) | (1 << s_simd[3])) == 15;
+  const int simd = four ? s_simd[w] : w;
+  const int nrb = (p.R + 15) / 16;
+  const int gb0 = qg * nrb / p.nqg, gcnt = (qg + 1) * nrb / p.nqg - gb0;
+  const int wr = (simd + (slot & 1 ? 2 : 0)) & 3;
+  const int nq = __builtin_amdgcn_readfirstlane(gcnt / 4 + (wr < gcnt % 4 ? 1 : 0));  // blocks of this wave
+  const int row0 = 16 * __builtin_amdgcn_readfirstlane(gb0 + wr * (gcnt / 4) + min(wr, gcnt % 4));
 
   const int ntiles = (k1 - k0 + kKeyTile - 1) / kKeyTile;
-  // Tile t lives in buffer t % 3: it is requested at step t - 2 (into the
-  // buffer tile t - 3 left, which every wave is past) and waited for at the
-  // end of step t - 1, with tile t + 1's loads left in flight.  Tiles past
-  // the end re-read the last key and are never used.
-  if (ntiles > 0) {
-    KT::issue(K, k0, k1, kt0, w, lane);
-    KT::issue(K, min(k0 + kKeyTile, k1 - 1), k1, kt1, w, lane);
-    lds_fill_barrier_but<KT::kLoadsPerWave>();
-  }
-  auto step = [&](auto par, int t) {
-    constexpr int PAR = decltype(par)::value;
-    const int tb = k0 + t * kKeyTile;
-    KT::issue(K, min(tb + 2 * kKeyTile, k1 - 1), k1, ktile(std::integral_constant<int, (PAR + 2) % 3>{}), w, lane);
-    if (active) {
-      if (tb + kKeyTile <= k1)
-        stats_tile<D, false>(ktile(par), bq, m, sum, tb, k1, lr, lg, sc);
-      else
-        stats_tile<D, true>(ktile(par), bq, m, sum, tb, k1, lr, lg, sc);
+  // Tiles past the end re-read the last key and are never used.
+  auto issue = [&](auto i, int t) { KT::issue(K, min(k0 + t * kKeyTile, k1 - 1), k1, ktile(i), w, lane); };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+
+  // Tile t lives in buffer t % 3.  A wave holds a tile's operands in
+  // registers, so a buffer is free once every wave has read it: the barrier
+  // of step t tells that tile t + 1 has landed and that tile t's buffer can
+  // take tile t + 3 (tile t + 2 stays in flight across it).
+  auto walk = [&](auto &&before, auto &&step, auto &&last) {
+    if (ntiles == 0) return;
+    issue(I0{}, 0);
+    issue(I1{}, 1);
+    issue(I2{}, 2);
+    lds_fill_barrier_but<2 * KT::kLoadsPerWave>();
+    before();
+    int t = 0;
+    for (; t + 3 < ntiles; t += 3) {
+      step(I0{}, t);
+      step(I1{}, t + 1);
+      step(I2{}, t + 2);
     }
-    lds_fill_barrier_but<KT::kLoadsPerWave>();
+    if (t + 1 < ntiles) step(I0{}, t++);
+    if (t + 1 < ntiles) step(I1{}, t++);
+    last(t);
+    lds_fill_barrier();  // every load in flight lands before the workgroup's LDS is released
   };
-  int t = 0;
-  for (; t + 2 < ntiles; t += 3) {
-    step(std::integral_constant<int, 0>{}, t);
-    step(std::integral_constant<int, 1>{}, t + 1);
-    step(std::integral_constant<int, 2>{}, t + 2);
-  }
-  if (t < ntiles) step(std::integral_constant<int, 0>{}, t);
-  if (t + 1 < ntiles) step(std::integral_constant<int, 1>{}, t + 1);
-  if (ntiles > 0) lds_fill_barrier();  // every load in flight lands before the workgroup's LDS is released
 
-  if (!active) return;
+  // A wave of NQ query blocks.  Its matrix work runs one block ahead of its
+  // softmax work, across the tile's end too: the last block's products hand
+  // their operand registers to tile t + 1, whose block 0 is multiplied under
+  // the softmax of the last block, so neither the LDS reads nor the last
+  // softmax stand alone.
+  auto wave = [&](auto nqc) {
+    constexpr int NQ = decltype(nqc)::value;
+    // Query rows -> bf16 B operands (round to nearest even), zero past R.  All
+    // loads are issued before any is used (rows clamped rather than branched
+    // on), so the prologue costs one round trip.
+    bf16x8 bq[NQ][KS];
+    {
+      u32x4 raw[NQ][KS][2];
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int rc = min(row0 + qb * 16 + lr, p.R - 1);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          const float *src = Q + (int64_t)rc * D + 32 * s + 8 * lg;
+          raw[qb][s][0] = ld16(src);
+          raw[qb][s][1] = ld16(src + 4);
+        }
+      }
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int row = row0 + qb * 16 + lr;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          const u32x4 a = raw[qb][s][0], c = raw[qb][s][1];
+          u32x4 pk = {pack_bf16(__uint_as_float(a.x), __uint_as_float(a.y)),
+                      pack_bf16(__uint_as_float(a.z), __uint_as_float(a.w)),
+                      pack_bf16(__uint_as_float(c.x), __uint_as_float(c.y)),
+                      pack_bf16(__uint_as_float(c.z), __uint_as_float(c.w))};
+          if (row >= p.R) pk = u32x4{0, 0, 0, 0};
+          bq[qb][s] = as_bf16x8(pk);
+        }
+      }
+    }
+    float m[NQ], sum[NQ];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) { m[qb] = kFloor; sum[qb] = 0.f; }
+    KeyOps<D> a;
+    f32x4 cur[4], nxt[4];
+    auto take = [&]() {
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) cur[kb] = nxt[kb];
+    };
+    walk(
+        [&]() {
+          key_operands<D>(kt0, lr, lg, a);
+          key_products<D>(a, bq[0], cur);
+          // The first key split also leaves the bf16 queries for the column pass.
+          if (ks == 0) {
+      #pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) {
+              const int row = row0 + qb * 16 + lr;
+              if (row < p.R) {
+      #pragma unroll
+                for (int s = 0; s < KS; ++s) st16(Qb + (int64_t)row * D + 32 * s + 8 * lg, as_u32x4(bq[qb][s]));
+              }
+            }
+          }
+        },
+        [&](auto par, int t) {
+          constexpr int NEXT = (decltype(par)::value + 1) % 3;
+#pragma unroll
+          for (int qb = 0; qb + 2 < NQ; ++qb) {
+            key_products<D>(a, bq[qb + 1], nxt);
+            stats_rows<false>(cur, m[qb], sum[qb], 0, k1, lg, sc);
+            interleave_mfma_valu<4 * KS, 4>();
+            take();
+          }
+          lds_fill_barrier_but<KT::kLoadsPerWave>();
+          issue(par, t + 3);
+          if constexpr (NQ >= 2) {
+            key_products<D>(a, bq[NQ - 1], nxt);
+            key_operands<D>(ktile(std::integral_constant<int, NEXT>{}), lr, lg, a);
+            stats_rows<false>(cur, m[NQ - 2], sum[NQ - 2], 0, k1, lg, sc);
+#pragma unroll
+            for (int i = 0; i < 4 * KS; ++i) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+            take();
+          } else {
+            key_operands<D>(ktile(std::integral_constant<int, NEXT>{}), lr, lg, a);
+          }
+          key_products<D>(a, bq[0], nxt);
+          stats_rows<false>(cur, m[NQ - 1], sum[NQ - 1], 0, k1, lg, sc);
+          interleave_mfma_valu<4 * KS, 4>();
+          take();
+        },
+        [&](int t) {  // the last tile may end past the split
+          const int tb = k0 + t * kKeyTile;
+#pragma unroll
+          for (int qb = 0; qb < NQ; ++qb) {
+            if (qb + 1 < NQ) key_products<D>(a, bq[qb + 1], nxt);
+            stats_rows<true>(cur, m[qb], sum[qb], tb, k1, lg, sc);
+            if (qb + 1 < NQ) take();
+          }
+        });
 
-  // Combine the four lane groups that share a query row, then store.
+    // Combine the four lane groups that share a query row, then store.
 #pragma unroll
-  for (int qb = 0; qb < 4; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
 #pragma unroll
-    for (int mask = 16; mask <= 32; mask <<= 1) {
-      const float mo = shfl_xor(m[qb], mask), so = shfl_xor(sum[qb], mask);
-      const float M = fmaxf(m[qb], mo);
-      sum[qb] = sum[qb] * fast_exp2(m[qb] - M) + so * fast_exp2(mo - M);
-      m[qb] = M;
+      for (int mask = 16; mask <= 32; mask <<= 1) {
+        const float mo = shfl_xor(m[qb], mask), so = shfl_xor(sum[qb], mask);
+        const float M = fmaxf(m[qb], mo);
+        sum[qb] = sum[qb] * fast_exp2(m[qb] - M) + so * fast_exp2(mo - M);
+        m[qb] = M;
+      }
+      const int row = row0 + qb * 16 + lr;
+      if (lg == 0 && row < p.R) {
+        const float mc = m[qb] <= kFloor ? kNegInf : m[qb];
+        stg(p.part + ((int64_t)u * p.nks + ks) * p.R + row, make_float2(mc, sum[qb]));
+      }
     }
-    const int row = row0 + qb * 16 + lr;
-    if (lg == 0 && row < p.R) {
-      const float mc = m[qb] <= kFloor ? kNegInf : m[qb];
-      stg(p.part + ((int64_t)u * p.nks + ks) * p.R + row, make_float2(mc, sum[qb]));
-    }
+  };
+  switch (nq) {  // wave-uniform; every wave makes the same barriers
+    case 4: wave(std::integral_constant<int, 4>{}); break;
+    case 3: wave(std::integral_constant<int, 3>{}); break;
+    case 2: wave(std::integral_constant<int, 2>{}); break;
+    case 1: wave(std::integral_constant<int, 1>{}); break;
+    default:  // no rows: only stage tiles
+      walk([]() {},
+           [&](auto par, int t) {
+             lds_fill_barrier_but<KT::kLoadsPerWave>();
+             issue(par, t + 3);
+           },
+           [](int) {});
   }
 }
 

@@ -63,6 +63,16 @@ __device__ __forceinline__ float2 ldg(const float2 *p) {
 __device__ __forceinline__ void stg(float2 *p, float2 v) {
   st8(p, u32x2{__float_as_uint(v.x), __float_as_uint(v.y)});
 }
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32);
+}
+template <typename T>
+__device__ __forceinline__ const T *uniform(const T *p) {
+  return reinterpret_cast<const T *>(uniform(reinterpret_cast<uint64_t>(p)));
+}
 constexpr int kXcds = 8;  // MI355X: 8 accelerator complex dies, 32 CUs each
 
 // D = A(16x32) * B(32x16) + C on the matrix cores.  Lane l holds row l%16 of A

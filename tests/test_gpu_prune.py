@@ -284,6 +284,35 @@ def test_fusion_passes_over_far_tiles(dev, orc, d, values):
             assert np.abs(got - ref).max() <= bound, (n, l, np.abs(got - ref).max(), bound)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,W", [(1, 1), (1, 17), (3, 16), (5, 13), (7, 64), (16, 16), (1, 257), (16, 64)])
+def test_window_scores_over_row_and_tile_counts(dev, orc, d, G, W):
+    """Window scores of every token at row counts around the 16-row block, the
+    wave and the workgroup (1 to 64 blocks, dealt unevenly), and key counts
+    around the 64-key tile and the ring of three tiles."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    from synthgen.device import to_host_bf16
+    gen = np.random.default_rng(G * 1000 + W)
+    params = vc.make_params(0.5, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED)
+    n = [1, 63, 64, 65, 129, 193, 257, 321]
+    B = len(n)
+    mk = lambda *s: torch.from_numpy(gen.standard_normal(s).astype(np.float32)).to(dev)
+    K = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
+    V = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
+    Q = [mk(B, G, W, d).to(torch.bfloat16).float() for _ in range(2)]
+    pc = PruneCall(B, 2, G, 1, d, W, n, params, K, V, Q)
+    pc.run()
+    torch.cuda.synchronize()
+    off, _ = vc.viscache_prune_score_offsets(pc.shape, params)
+    S = pc.ws[off:off + 8 * sum(n)].view(torch.float32).cpu().numpy().reshape(2, -1)
+    for l in range(2):
+        for b in range(B):
+            o = sum(n[:b])
+            ref = orc.scores_unit(to_host_bf16(K[l])[o:o + n[b]], Q[l][b].reshape(-1, d).cpu().numpy())
+            assert rel_err(ref, S[l][o:o + n[b]]) <= SCORE_TOL, (l, b)
+
+
 def test_mu_one_is_plain_pruning(dev, orc, sg):
     w = _custom(sg)
     r = Run(w, dev, mu=1.0, vfp32=True)
