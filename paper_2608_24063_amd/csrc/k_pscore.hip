@@ -187,6 +187,11 @@ __global__ __launch_bounds__(256, 2) void k_pscore(PrunePlan p, uint32_t *plan_d
     // Smallest position among the wave's rows (-1 if a row is missing): key
     // tiles wholly at or before it need no causal mask in either pass.
     const int wmin = __builtin_amdgcn_readfirstlane(wave_min(min(min(pos[0], pos[1]), min(pos[2], pos[3]))));
+    // Largest one: key tiles wholly past it give the wave nothing, and it only
+    // keeps the barriers.  (Of the four or five tiles of a group that reach
+    // past its first row, a wave needs two; 3200 tokens, 28 layers, 28 / 4
+    // heads, d = 128: 2.10 -> 2.02 ms.)
+    const int wmax = -__builtin_amdgcn_readfirstlane(wave_min(min(min(-pos[0], -pos[1]), min(-pos[2], -pos[3]))));
 
     // ---------------- pass A: row statistics over keys 0 .. kend-1
     const int ntA = (kend + 63) / 64;
@@ -200,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void k_pscore(PrunePlan p, uint32_t *plan_d
       const int tb = t * 64;
       // The other buffer was last read in tile t - 1, before the last barrier.
       if (t + 1 < ntA) KT::issue(Kv, Kt, n, tb + 64, kend, PAR ? kt0 : kt1, w, lane);
-      if (active) {
+      if (active && tb <= wmax) {
         const uint16_t *kl = PAR ? kt1 : kt0;
         // Two halves of 32 keys (operands of one half in registers at a time);
         // each half updates the rows' running max and sum.  Tiles wholly at or
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(256, 2) void k_pscore(PrunePlan p, uint32_t *plan_d
         pend = tb + tid < n ? ldg(cp + tb + tid) : 0.f;
       }
       float col[4] = {0.f, 0.f, 0.f, 0.f};
-      if (active) {
+      if (active && tb <= wmax) {
         const uint16_t *kl = PAR ? kt1 : kt0;
         const bool interior = tb + 63 <= wmin;  // wave-uniform
 #pragma unroll

@@ -484,6 +484,37 @@ def _prefill_direct(dev, n, L, Hq, Hkv, d, W, K, V, Kt, Q, rr=0.25):
     return pc, S
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,W", [(1, 1), (3, 5), (2, 70), (5, 128)])
+def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W):
+    """Prefill scores of every token at lengths around the 64-key tile and the
+    256-row group (tiles without a mask, on the diagonal and past a wave's
+    rows; row groups that straddle heads; tiles of visual and text keys)."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    from synthgen.device import to_host_bf16
+    gen = np.random.default_rng(G * 1000 + W)
+    params = vc.make_params(0.5, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, score_queries=vc.VC_SCORE_PREFILL)
+    n = [1, 63, 64, 65, 191, 193, 256, 321, 449]
+    B = len(n)
+    mk = lambda *s: torch.from_numpy(gen.standard_normal(s).astype(np.float32)).to(dev)
+    K = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
+    V = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
+    T = [mk(B, 1, W, d).to(torch.bfloat16) for _ in range(2)]
+    Q = [mk(G * (sum(n) + B * W), d).to(torch.bfloat16).float() for _ in range(2)]
+    pc = PruneCall(B, 2, G, 1, d, W, n, params, K, V, Q, k_text=T)
+    pc.run()
+    torch.cuda.synchronize()
+    off, _ = vc.viscache_prune_score_offsets(pc.shape, params)
+    S = pc.ws[off:off + 8 * sum(n)].view(torch.float32).cpu().numpy().reshape(2, -1)
+    for l in range(2):
+        for b in range(B):
+            o = sum(n[:b])
+            q = Q[l][G * (o + b * W):G * (o + n[b] + (b + 1) * W)].reshape(G, n[b] + W, d).cpu().numpy()
+            ref = orc.scores_unit_prefill(to_host_bf16(K[l])[o:o + n[b]], to_host_bf16(T[l])[b, 0], q)
+            assert rel_err(ref, S[l][o:o + n[b]], floor=1e-30) <= 1e-4, (l, b)
+
+
 def test_prefill_empty_sequences_in_batch(dev, orc):
     """Sequences with no visual token: their text rows are still queries but
     there is nothing to score or keep."""
