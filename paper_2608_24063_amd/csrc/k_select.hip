@@ -7,12 +7,22 @@
 // thread holds a contiguous run of up to PER scores in registers.  Scores are
 // non-negative fp32, so their bit patterns order like the values.  The k-th
 // and n_surv-th largest bit patterns are found exactly by a most-significant-
-// digit radix select over the 31 value bits (digits of 8, 8, 8 and 7 bits,
-// both cuts in the same passes): each wave counts the digits of the keys that
-// still match a cut's prefix into its own LDS histogram, and two waves scan
-// the summed histograms for the bin holding the wanted rank.  Ties at a
-// threshold go to the lowest indices, and block-wide prefix sums (DPP wave
-// scans) compact kept and dropped indices in ascending token order.
+// digit radix select over the 31 value bits (digits of 11, 10 and 10 bits,
+// both cuts in the same passes): the keys that still match a cut's prefix are
+// counted by digit in an LDS histogram, and two waves scan the histograms for
+// the bin holding the wanted rank.  Ties at a threshold go to the lowest
+// indices, and one block-wide prefix sum (DPP wave scans) gives every thread
+// the places of its kept and dropped tokens, in ascending token order.
+//
+// A chain of LDS round trips and barriers bounds it, so the digits are wide
+// (three passes; the first one's 11 bits also spread the scores, which share
+// few exponents, over several times more bins than 8 bits do), all histograms
+// are cleared while the scores are on their way, and the ties still wanted
+// and the dropped tokens' places follow from the passes and the one scan.
+// Against digits of 8, 8, 8 and 7 bits in a histogram a wave and two scans
+// (stage times, 5 us of them the timing's own): 512 keys 10.2 -> 8.5 us, 3136
+// 14.2 -> 11.0, 12544 22.4 -> 18.0, eight sequences of 14k to 23k (672 units)
+// 102 -> 79.
 #include "vc_device.h"
 #include "vc_internal.h"
 
@@ -20,10 +30,9 @@ namespace vc {
 
 namespace {
 
-// Exclusive prefix over the block of four counters per thread, plus totals.
+// Exclusive prefix over the block of four counters per thread.
 template <int kWaves>
-__device__ __forceinline__ void block_scan4(const uint32_t v[4], uint32_t excl[4], uint32_t tot[4],
-                                            uint32_t (*wt)[kWaves]) {
+__device__ __forceinline__ void block_scan4(const uint32_t v[4], uint32_t excl[4], uint32_t (*wt)[kWaves]) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint32_t inc[4];
 #pragma unroll
@@ -34,87 +43,70 @@ __device__ __forceinline__ void block_scan4(const uint32_t v[4], uint32_t excl[4
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    uint32_t before = 0, all = 0;
+    uint32_t before = 0;
 #pragma unroll
-    for (int q = 0; q < kWaves; ++q) {
-      const uint32_t x = wt[c][q];
-      before += q < w ? x : 0u;
-      all += x;
-    }
+    for (int q = 0; q < kWaves; ++q) before += q < w ? wt[c][q] : 0u;
     excl[c] = before + inc[c] - v[c];
-    tot[c] = all;
   }
-  __syncthreads();
 }
 
-// One radix pass for both cuts: digits of `wd` bits at bit `sh`.  On entry
-// pre[c] holds the cut's value bits above the digit and rank[c] the wanted
-// rank (1-based, descending) among the keys sharing them; on exit the digit
-// is fixed and the rank is relative to it.  A rank of 0 (nothing wanted)
-// stays 0.
-template <int kWaves, int PER>
-__device__ __forceinline__ void radix_pass(const uint32_t (&key)[PER], int cnt, int sh, int wd, uint32_t (&pre)[2],
-                                           uint32_t (&rank)[2], uint32_t (*hist)[2][256], uint32_t (*res)[2]) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // This wave's histogram (the previous pass's scans finished before the
-  // barrier that ended it).
+// The bin, in descending order, that holds rank r (1-based) among the
+// histogram's 64 PER bins, and the rank within it; (0, 0) for r = 0.  Whole
+// wave: lane l sums bins PER l .. PER l + PER - 1 of the descending order, then
+// the hit lane's bins are spread over the lanes.
+template <int PER>
+__device__ __forceinline__ void find_bin(const uint32_t *hist, uint32_t r, uint32_t *res) {
+  constexpr int kBins = 64 * PER;
+  const int lane = threadIdx.x & 63;
+  uint32_t tot = 0u;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) (&hist[w][0][0])[lane + 64 * i] = 0u;
-  __builtin_amdgcn_wave_barrier();
-  const int top = sh + wd;
-  const uint32_t dm = (1u << wd) - 1u;
-  const uint32_t p0 = top >= 31 ? 0u : pre[0] >> top, p1 = top >= 31 ? 0u : pre[1] >> top;
-  // While both cuts share their prefix (always in the first pass), one
-  // histogram serves both.
+  for (int i = 0; i < PER; i += 4) {
+    const u32x4 h = *reinterpret_cast<const u32x4 *>(hist + kBins - PER * (lane + 1) + i);
+    tot += (h.x + h.y) + (h.z + h.w);
+  }
+  const uint32_t incl = wave_incl_scan(tot);
+  const uint64_t hit = __builtin_amdgcn_ballot_w64(r > 0 && incl - tot < r && r <= incl);
+  uint32_t dg = 0u, nr = 0u;
+  if (hit) {
+    const int src = __builtin_ctzll(hit);
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(incl - tot), src);
+    const int bin = kBins - 1 - PER * src - lane;  // descending within the lane's bins
+    const uint32_t h = lane < PER ? hist[max(bin, 0)] : 0u;
+    const uint32_t in2 = wave_incl_scan(h) + before;
+    const uint64_t hit2 = __builtin_amdgcn_ballot_w64(in2 - h < r && r <= in2);
+    const int src2 = __builtin_ctzll(hit2);
+    dg = (uint32_t)(kBins - 1 - PER * src - src2);
+    nr = r - (uint32_t)__builtin_amdgcn_readlane((int)(in2 - h), src2);
+  }
+  if (lane == 0) {
+    res[0] = dg;
+    res[1] = nr;
+  }
+}
+
+// One radix pass for both cuts over the digit of `64 PERB`-bin histograms at
+// bit `sh`.  On entry pre[c] holds the cut's value bits above the digit and
+// rank[c] the wanted rank (1-based, descending) among the keys sharing them;
+// on exit the digit is fixed and the rank is relative to it.  A rank of 0
+// (nothing wanted) stays 0.  While both cuts share their prefix (always in
+// the first pass), one histogram serves both.  hist: zeroed.
+template <int PERB, int PER>
+__device__ __forceinline__ void radix_pass(const uint32_t (&key)[PER], int cnt, int sh, uint32_t (&pre)[2],
+                                           uint32_t (&rank)[2], uint32_t *hist, uint32_t (*res)[2]) {
+  constexpr int kBins = 64 * PERB;
+  const int w = threadIdx.x >> 6;
+  const uint32_t p0 = pre[0] / kBins >> sh, p1 = pre[1] / kBins >> sh;
   const bool same = p0 == p1;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     if (i < cnt) {
-      const uint32_t hi = top >= 31 ? 0u : key[i] >> top;
-      const uint32_t dg = (key[i] >> sh) & dm;
-      if (hi == p0) atomicAdd(&hist[w][0][dg], 1u);
-      if (!same && hi == p1) atomicAdd(&hist[w][1][dg], 1u);
+      const uint32_t hi = key[i] / kBins >> sh, dg = (key[i] >> sh) & (kBins - 1);
+      if (hi == p0) atomicAdd(&hist[dg], 1u);
+      if (!same && hi == p1) atomicAdd(&hist[kBins + dg], 1u);
     }
   }
   __syncthreads();
-  if (w < 2) {
-    // Wave c scans cut c: lane l owns bins 255-4l .. 252-4l (descending).
-    const int c = w, hc = same ? 0 : w;
-    uint32_t b4[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int q = 0; q < kWaves; ++q) {
-      const uint4 h = *reinterpret_cast<const uint4 *>(&hist[q][hc][252 - 4 * lane]);
-      b4[0] += h.w;
-      b4[1] += h.z;
-      b4[2] += h.y;
-      b4[3] += h.x;
-    }
-    const uint32_t tot = (b4[0] + b4[1]) + (b4[2] + b4[3]);
-    const uint32_t incl = wave_incl_scan(tot);
-    const uint32_t excl = incl - tot;
-    const uint32_t r = rank[c];
-    const uint64_t hit = __builtin_amdgcn_ballot_w64(r > 0 && excl < r && r <= incl);
-    if (hit) {
-      const int src = __builtin_ctzll(hit);
-      if (lane == src) {
-        uint32_t cum = excl, dg = 0u, nr = 0u;
-#pragma unroll
-        for (int j = 3; j >= 0; --j) {  // pick the first bin (descending) that reaches the rank
-          const uint32_t j2 = 3 - j;
-          if (cum < r && r <= cum + b4[j2] && nr == 0u) {
-            dg = 255u - 4u * lane - j2;
-            nr = r - cum;
-          }
-          cum += b4[j2];
-        }
-        res[c][0] = dg;
-        res[c][1] = nr;
-      }
-    } else if (lane == 0) {
-      res[c][0] = 0u;
-      res[c][1] = 0u;
-    }
-  }
+  if (w < 2) find_bin<PERB>(hist + (same || w == 0 ? 0 : kBins), w ? rank[1] : rank[0], res[w]);
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -126,8 +118,11 @@ __device__ __forceinline__ void radix_pass(const uint32_t (&key)[PER], int cnt, 
 template <int kThreads, int PER>
 __global__ __launch_bounds__(kThreads) void k_select(PrunePlan p) {
   constexpr int kWaves = kThreads / 64;
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kWaves][2][256];  // per-wave digit counts per cut
-  __shared__ uint32_t res[2][2];                                          // per cut: digit, rank within it
+  // Digit counts: 2048 bins of the first pass, two times 1024 (a cut each) of
+  // the second and of the third.
+  constexpr int kHist = 2048 * 3;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kHist];
+  __shared__ uint32_t res[3][2][2];  // per pass and cut: digit, rank within it
   __shared__ uint32_t wt[4][kWaves];
 
   const int u = blockIdx.x;  // ((l * B) + b) * Hkv + g, l < h
@@ -165,13 +160,15 @@ __global__ __launch_bounds__(kThreads) void k_select(PrunePlan p) {
     key[i] = (x & 0x80000000u) ? 0x7FFFFFFFu : x;
   }
 
+  for (int i = 4 * tid; i < kHist; i += 4 * kThreads) *reinterpret_cast<u32x4 *>(hist + i) = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+
   // Thresholds: the k-th and n_surv-th largest bit patterns (none wanted:
   // above every key).
   uint32_t pre[2] = {0u, 0u}, rank[2] = {(uint32_t)k, (uint32_t)nsv};
-  radix_pass<kWaves, PER>(key, cnt, 23, 8, pre, rank, hist, res);
-  radix_pass<kWaves, PER>(key, cnt, 15, 8, pre, rank, hist, res);
-  radix_pass<kWaves, PER>(key, cnt, 7, 8, pre, rank, hist, res);
-  radix_pass<kWaves, PER>(key, cnt, 0, 7, pre, rank, hist, res);
+  radix_pass<32, PER>(key, cnt, 20, pre, rank, hist, res[0]);
+  radix_pass<16, PER>(key, cnt, 10, pre, rank, hist + 2048, res[1]);
+  radix_pass<16, PER>(key, cnt, 0, pre, rank, hist + 4096, res[2]);
   const uint32_t tk = k > 0 ? pre[0] : 0xFFFFFFFFu, ts = nsv > 0 ? pre[1] : 0xFFFFFFFFu;
 
   // Counts above and at each threshold; ties fill in ascending index order.
@@ -184,50 +181,37 @@ __global__ __launch_bounds__(kThreads) void k_select(PrunePlan p) {
       c4[2] += key[i] > ts;
       c4[3] += key[i] == ts;
     }
-  uint32_t ex[4], tot4[4];
-  block_scan4<kWaves>(c4, ex, tot4, wt);
-  const uint32_t need_k = k > 0 ? (uint32_t)k - tot4[0] : 0u;
-  const uint32_t need_s = (uint32_t)nsv - tot4[2];
+  uint32_t ex[4];
+  block_scan4<kWaves>(c4, ex, wt);
+  // The ranks within the thresholds are the ties wanted.  The kept tokens are
+  // among the survivors, so the dropped ones before a thread are the
+  // difference of both counts.
+  const uint32_t need_k = rank[0], need_s = rank[1];
   uint32_t ek = ex[1], es = ex[3];
+  uint32_t pk = ex[0] + min(ek, need_k), pd = ex[2] + min(es, need_s) - pk;
 
-  uint32_t keepmask = 0u, dropmask = 0u;
-  uint32_t nkeep = 0, ndrop = 0;
+  int32_t *idx = reinterpret_cast<int32_t *>(idx_base) + orow + (int64_t)g * k;
+  int32_t *drop = reinterpret_cast<int32_t *>(drop_base) + drow + (int64_t)g * r;
 #pragma unroll
   for (int i = 0; i < PER; ++i)
     if (i < cnt) {
       const uint32_t x = key[i];
-      bool kp = false;
-      if (k > 0) {
-        kp = x > tk || (x == tk && ek < need_k);
-        if (x == tk) ++ek;
-      }
+      const bool kp = x > tk || (x == tk && ek < need_k);
       const bool sv = x > ts || (x == ts && es < need_s);
-      if (x == ts) ++es;
-      if (kp) { keepmask |= 1u << i; ++nkeep; }
-      else if (sv) { dropmask |= 1u << i; ++ndrop; }
-    }
-
-  const uint32_t c2[4] = {nkeep, ndrop, 0, 0};
-  block_scan4<kWaves>(c2, ex, tot4, wt);
-
-  int32_t *idx = reinterpret_cast<int32_t *>(idx_base) + orow + (int64_t)g * k;
-  int32_t *drop = reinterpret_cast<int32_t *>(drop_base) + drow + (int64_t)g * r;
-  uint32_t pk = ex[0], pd = ex[1];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    if ((keepmask >> i) & 1u) {
-      if (pk < (uint32_t)k) {
-        stg(idx + pk, (int32_t)(v0 + i));
-        // The first kept token of a fusion job: dropped tokens before it.
-        if (pk % kFuseRows == 0) stg(p.jstart + jb + pk / kFuseRows, (int32_t)pd);
+      ek += x == tk;
+      es += x == ts;
+      if (kp) {
+        if (pk < (uint32_t)k) {
+          stg(idx + pk, (int32_t)(v0 + i));
+          // The first kept token of a fusion job: dropped tokens before it.
+          if (pk % kFuseRows == 0) stg(p.jstart + jb + pk / kFuseRows, (int32_t)pd);
+        }
+        ++pk;
+      } else if (sv) {
+        if (pd < (uint32_t)r) stg(drop + pd, (int32_t)(v0 + i));
+        ++pd;
       }
-      ++pk;
     }
-    if ((dropmask >> i) & 1u) {
-      if (pd < (uint32_t)r) stg(drop + pd, (int32_t)(v0 + i));
-      ++pd;
-    }
-  }
 }
 
 }  // namespace

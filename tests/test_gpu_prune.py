@@ -313,6 +313,42 @@ def test_window_scores_over_row_and_tile_counts(dev, orc, d, G, W):
             assert rel_err(ref, S[l][o:o + n[b]]) <= SCORE_TOL, (l, b)
 
 
+@pytest.mark.parametrize("n", [[1, 2, 255], [2047, 2048, 3], [2049], [8192, 63], [8193], [16384], [16385, 1], [32768]])
+@pytest.mark.parametrize("distinct", [3, 0])
+def test_selection_is_the_exact_ranking(dev, n, distinct):
+    """Kept and dropped tokens are exactly the top ranks of the GPU's own
+    scores, ties to the lowest index: lengths around the switches of the
+    workgroup's size, keys drawn from three rows (long runs of equal scores at
+    every cut) and all different."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    gen = torch.Generator(device=dev).manual_seed(sum(n) + distinct)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev)
+    d, B = 64, len(n)
+    params = vc.make_params(0.2, h=2, m=0.75)
+    K = [rnd(sum(n), d) for _ in range(2)]
+    if distinct:
+        K = [k[torch.randint(distinct, (sum(n),), generator=gen, device=dev)] for k in K]
+    K = [k.to(torch.bfloat16) for k in K]
+    V = [rnd(sum(n), d).to(torch.bfloat16) for _ in range(2)]
+    Q = [rnd(B, 1, 4, d) for _ in range(2)]
+    pc = PruneCall(B, 2, 1, 1, d, 4, n, params, K, V, Q, with_drop=True)
+    pc.run()
+    torch.cuda.synchronize()
+    off, _ = vc.viscache_prune_score_offsets(pc.shape, params)
+    S = pc.ws[off:off + 8 * sum(n)].view(torch.float32).cpu().numpy().reshape(2, -1)
+    for l in range(2):
+        for b in range(B):
+            o = sum(n[:b])
+            s = S[l][o:o + n[b]]
+            order = np.lexsort((np.arange(n[b]), -s.astype(np.float64)))
+            k, ns = pc.k[b * 2 + l], pc.n_surv[b * 2 + l]
+            r0, r1 = pc.unit_rows(l, b, 0)
+            d0, d1 = pc.unit_drop_rows(l, b, 0)
+            np.testing.assert_array_equal(pc.idx_out[l][r0:r1].cpu().numpy(), np.sort(order[:k]))
+            np.testing.assert_array_equal(pc.drop_out[l][d0:d1].cpu().numpy(), np.sort(order[k:ns]))
+
+
 def test_mu_one_is_plain_pruning(dev, orc, sg):
     w = _custom(sg)
     r = Run(w, dev, mu=1.0, vfp32=True)
