@@ -160,13 +160,14 @@ class DecodeCache:
             self._layer_caches = [
                 vc_cache(self.k_pool.data_ptr(), self.v_pool.data_ptr(), self.row_off[l * per:].data_ptr(),
                          self.cap[l * per:].data_ptr(), self.len[l * per:].data_ptr()) for l in range(self.L)]
-            self.layer_caps = [max(self.caps_host[l * per:(l + 1) * per]) for l in range(self.L)]
-            nb = max(viscache_decode_step_workspace_bytes(self.layer_shape, c) for c in self.layer_caps)
-            self.layer_ws_bytes = max(nb, 256)
+            # One row bound for all layers: the workspace's layout follows from
+            # it, and the arrival counters that a call leaves at zero have to
+            # be where the next layer's call looks for them.
+            self.layer_ws_bytes = max(viscache_decode_step_workspace_bytes(self.layer_shape, self.max_cap), 256)
             self.layer_ws = torch.zeros((self.layer_ws_bytes,), dtype=torch.uint8, device=self.k_pool.device)
         for l in range(self.L):
             viscache_decode_step(self.layer_shape, self._layer_caches[l], k_new[l].data_ptr(), v_new[l].data_ptr(),
-                                 q[l].data_ptr(), out[l].data_ptr(), scale, self.layer_caps[l],
+                                 q[l].data_ptr(), out[l].data_ptr(), scale, self.max_cap,
                                  self.layer_ws.data_ptr(), self.layer_ws_bytes, _stream())
 
     def quantize(self, nq) -> None:

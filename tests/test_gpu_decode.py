@@ -270,3 +270,38 @@ def test_decode_many_units_and_long_unit(dev, orc, sg):
                     assert np.all(o[l, b, g * G:(g + 1) * G] == 0)
                     continue
                 _check_out(orc, q[l, b, h], K[r0:r0 + n], V[r0:r0 + n], o[l, b, h], scale, f"u={u} n={n}")
+
+
+@pytest.mark.parametrize("d,Hkv", [(64, 1), (128, 2), (128, 65)])
+def test_step_layers_with_unlike_capacities(dev, sg, d, Hkv):
+    """One launch per layer over layers whose capacities differ widely (the
+    pruned cache of a layer-wise budget), sharing one workspace: the results
+    and lengths of one launch for all layers, over several steps.  Calls of a
+    few units and of more than 64, units in one piece and in many, and more
+    pieces than the launch has workgroups for at the smallest bound.  The
+    piece bounds of the two launches differ, so results agree to fp32 rounding
+    (weights as bf16 pairs, within 2^-17)."""
+    from paper_2608_24063_amd.tensors import DecodeCache
+    L, B, G, steps = 4, 1, 2, 3
+    caps = []
+    for l, top in enumerate((5000, 40, 900, 2100)):
+        caps += [max(steps + 1, top // (1 + u % 7)) for u in range(B * Hkv)]
+    gen = torch.Generator(device=dev).manual_seed(d + Hkv)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev).to(torch.bfloat16)
+    a, b = (DecodeCache(L, B, Hkv * G, Hkv, d, caps, dev) for _ in range(2))
+    a.k_pool.copy_(rnd(*a.k_pool.shape))
+    a.v_pool.copy_(rnd(*a.v_pool.shape))
+    b.k_pool.copy_(a.k_pool)
+    b.v_pool.copy_(a.v_pool)
+    lens = torch.tensor([c - steps for c in caps], dtype=torch.int32)
+    a.len.copy_(lens)
+    b.len.copy_(lens)
+    oa, ob = (torch.empty((L, B, Hkv * G, d), dtype=torch.float32, device=dev) for _ in range(2))
+    for t in range(steps):
+        k, v, q = rnd(L, B, Hkv, d), rnd(L, B, Hkv, d), rnd(L, B, Hkv * G, d)
+        a.step_layers(k, v, q, oa, d ** -0.5)
+        b.step(k, v, q, ob, d ** -0.5)
+        torch.cuda.synchronize()
+        assert float((oa - ob).abs().max()) <= 2.0 ** -16 * float(a.v_pool.float().abs().max())
+        assert torch.equal(a.len, b.len) and a.len.cpu().tolist() == (lens + t + 1).tolist()
+    assert torch.equal(a.k_pool, b.k_pool) and torch.equal(a.v_pool, b.v_pool)
