@@ -23,7 +23,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 struct Layout {
   int32_t B, L, Hq, Hkv, d, W, G, R, h, Ls, mode, vfp32;
   int32_t nqg, nks, ncol, nmax;
-  int32_t prefill, pwg;
+  int32_t prefill, pwg, pring;
   int64_t Ntot;
   std::vector<int32_t> n, k, ns;       // n[B], k[B*L], ns[B*L]
   std::vector<int32_t> funit;          // fusion units, longest drop list first
@@ -110,6 +110,7 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
   const int64_t units = (int64_t)y.Ls * y.B * y.Hkv;
   int64_t rows = y.R;  // query rows of the longest unit
   y.pwg = 0;
+  y.pring = 0;
   if (y.prefill) {
     // Every prefill token queries: a unit has G * (n_b + W) rows, in groups
     // of 256.  Each of a unit's pwg workgroups owns every pwg-th group.  The
@@ -123,6 +124,21 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
     const int64_t groups = (rows + kStatsRows - 1) / kStatsRows;
     const int64_t per_wg = std::max<int64_t>(1, (groups * units + 4 * kScoreSlots) / (8 * kScoreSlots));
     y.pwg = (int32_t)std::min<int64_t>(groups, (groups + per_wg - 1) / per_wg);
+    // Key tiles go through a ring of three buffers, products ahead of the
+    // softmax, from kRingTokens tokens on (a sequence counting by its share of
+    // the (query, key) pairs); shorter ones through two, whose start and end
+    // cost less (the ring loads three tiles past each pass's end).  The call
+    // with the ring against two buffers (28 layers, 28 / 4 heads, d = 128):
+    // 6001 tokens 6742 / 7048 us, 3136 2000 / 2081, 2700 1737 / 1773, 2300
+    // 1383 / 1382, 1800 958 / 934, 1201 549 / 512.
+    constexpr double kRingTokens = 2304;
+    double pairs = 0, weighted = 0;
+    for (int32_t nb : y.n) {
+      const double N = (double)nb + y.W;
+      pairs += N * N;
+      weighted += N * N * N;
+    }
+    y.pring = weighted >= kRingTokens * pairs;
   }
   y.nqg = (int32_t)((rows + kStatsRows - 1) / kStatsRows);
   const int64_t base = std::max<int64_t>(1, units * y.nqg);
@@ -448,6 +464,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   pl.R = y.R; pl.h = y.h; pl.Ls = y.Ls; pl.mode = y.mode; pl.v_fp32 = y.vfp32;
   pl.nqg = y.nqg; pl.nks = y.nks; pl.ncol = y.ncol; pl.nmax = y.nmax;
   pl.pwg = y.pwg;
+  pl.pring = y.pring;
   pl.nfunits = (int32_t)y.funit.size();
   pl.nfwg = y.nfwg;
   pl.sc = (float)(1.4426950408889634 / std::sqrt((double)y.d));

@@ -59,6 +59,7 @@ struct PrunePlan {
   int32_t nfwg;       // fusion workgroups (persistent; a multiple of 8, the same number per XCD)
   int32_t nmax;       // max n_b
   int32_t pwg;        // prefill: workgroups per unit (each owns every pwg-th 256-row group)
+  int32_t pring;      // prefill: key tiles through a ring of three (long sequences) or two buffers
   float sc;           // log2(e) / sqrt(d)
   float tc;           // log2(e) / tau
   float mu;

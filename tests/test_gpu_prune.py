@@ -522,16 +522,19 @@ def _prefill_direct(dev, n, L, Hq, Hkv, d, W, K, V, Kt, Q, rr=0.25):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("G,W", [(1, 1), (3, 5), (2, 70), (5, 128)])
-def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W):
-    """Prefill scores of every token at lengths around the 64-key tile and the
-    256-row group (tiles without a mask, on the diagonal and past a wave's
-    rows; row groups that straddle heads; tiles of visual and text keys)."""
+@pytest.mark.parametrize("longest", [0, 6000])
+def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W, longest):
+    """Prefill scores of every token at lengths around the 64-key tile, the
+    ring of three tiles and the 256-row group (tiles without a mask, on the
+    diagonal and past a wave's rows; row groups that straddle heads; tiles of
+    visual and text keys).  A long sequence in the batch, which is not compared
+    itself, takes the others through the ring."""
     import paper_2608_24063_amd as vc
     from paper_2608_24063_amd.tensors import PruneCall
     from synthgen.device import to_host_bf16
     gen = np.random.default_rng(G * 1000 + W)
     params = vc.make_params(0.5, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, score_queries=vc.VC_SCORE_PREFILL)
-    n = [1, 63, 64, 65, 191, 193, 256, 321, 449]
+    n = [1, 63, 64, 65, 191, 193, 256, 321, 449] + ([longest] if longest else [])
     B = len(n)
     mk = lambda *s: torch.from_numpy(gen.standard_normal(s).astype(np.float32)).to(dev)
     K = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
@@ -545,6 +548,8 @@ def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W):
     S = pc.ws[off:off + 8 * sum(n)].view(torch.float32).cpu().numpy().reshape(2, -1)
     for l in range(2):
         for b in range(B):
+            if n[b] == longest:
+                continue
             o = sum(n[:b])
             q = Q[l][G * (o + b * W):G * (o + n[b] + (b + 1) * W)].reshape(G, n[b] + W, d).cpu().numpy()
             ref = orc.scores_unit_prefill(to_host_bf16(K[l])[o:o + n[b]], to_host_bf16(T[l])[b, 0], q)
