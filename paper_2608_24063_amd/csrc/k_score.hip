@@ -58,6 +58,32 @@ struct RowTileLds {
       __builtin_amdgcn_global_load_lds((const VC_GLOBAL void *)s, (VC_LDS_AS void *)(buf + ld * 512), 16, 0, 0);
     }
   }
+  // The same from a wave-uniform base: the 64 rows at src, of which `rows`
+  // exist.  src, rows and w are wave-uniform and `off` holds the lane's byte
+  // offsets in a full tile, whose loads then need no vector arithmetic.
+  __device__ static __forceinline__ uint32_t offset(int j, int w, int lane, int rlast) {
+    const int r = (w * kLoadsPerWave + j) * kRowsPerLoad + lane / kSlots;
+    return (uint32_t)min(r, rlast) * (D * 2) + ((lane % kSlots) ^ sw(r)) * 16;
+  }
+  __device__ static __forceinline__ void load(const uint16_t *src, uint32_t off, uint16_t *buf, int w, int j) {
+    const VC_GLOBAL char *s = (const VC_GLOBAL char *)src + off;
+    __builtin_amdgcn_global_load_lds((const VC_GLOBAL void *)s, (VC_LDS_AS void *)(buf + (w * kLoadsPerWave + j) * 512), 16,
+                                     0, 0);
+  }
+  __device__ static __forceinline__ void issue_uniform(const uint16_t *src, int rows,
+                                                       const uint32_t (&off)[kLoadsPerWave], uint16_t *buf, int w,
+                                                       int lane) {
+    if (rows >= 64) {
+#pragma unroll
+      for (int j = 0; j < kLoadsPerWave; ++j) load(src, off[j], buf, w, j);
+    } else {
+      int z = 0;  // (the lane's number taken again: nothing of this rare path is held across a loop)
+      asm volatile("" : "+s"(z));
+      lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)z));
+#pragma unroll
+      for (int j = 0; j < kLoadsPerWave; ++j) load(src, offset(j, w, lane, rows - 1), buf, w, j);
+    }
+  }
   // Operand of rows rb*16 + lr, k-elements 32*s + 8*lg .. + 8.
   __device__ static __forceinline__ bf16x8 operand(const uint16_t *buf, int rb, int s, int lr, int lg) {
     const int r = rb * 16 + lr;
@@ -413,6 +439,13 @@ __global__ __launch_bounds__(256, 2) void k_score_stats(PrunePlan p, uint32_t *p
 // global-to-LDS loads into a chunk-swizzled tile, one tile ahead), so the
 // product is Z (queries x keys): lane l sees key l%16 of each 16-key block and
 // rows 4*(l/16)+i, and accumulates exp2(z*sc - m_r) / sum_r per key.
+//
+// Bound like the first pass by the matrix and the vector unit, whose cycles
+// mostly add up.  The tile loads take their addresses from uniform bases and
+// lane offsets found once: one sequence of 3136 tokens 43.5 -> 42.2 us, 12.5k
+// 131 -> 129, three of 0.8k to 3.1k 91 -> 88.8; eight of 14k to 23k 1.48 ->
+// 1.43 ms in one run and even in another.  (In the first pass the same made
+// the statistics 2 to 4% slower.)
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256, 3) void k_score_colsum(PrunePlan p) {
@@ -428,10 +461,10 @@ __global__ __launch_bounds__(256, 3) void k_score_colsum(PrunePlan p) {
   const int u = lb / p.ncol;
   int ls, b, g;
   unit_coords(p, u, ls, b, g);
-  const int n = ldg(p.nb + b);
+  const int n = uniform(ldg(p.nb + b));
   if (c * kColKeys >= n) return;  // whole workgroup exits together
   const int64_t toff = ldg(p.toff + b);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const float sc = p.sc;
   const int R = p.R;
@@ -439,8 +472,8 @@ __global__ __launch_bounds__(256, 3) void k_score_colsum(PrunePlan p) {
 
   const uint16_t *K = reinterpret_cast<const uint16_t *>(ldg(p.lp + LP_K_IN * p.L + ls)) +
                       (toff * p.Hkv + (int64_t)g * n) * D;
-  const uint16_t *Qb = p.qbf + (int64_t)ls * p.B * p.Hq * p.W * D +
-                       ((int64_t)b * p.Hq + (int64_t)g * p.G) * p.W * D;
+  const uint16_t *Qb = uniform(p.qbf + (int64_t)ls * p.B * p.Hq * p.W * D +
+                               ((int64_t)b * p.Hq + (int64_t)g * p.G) * p.W * D);
 
   // Keys of this wave as B operands.
   const int key0 = c * kColKeys + w * 64;
@@ -453,7 +486,10 @@ __global__ __launch_bounds__(256, 3) void k_score_colsum(PrunePlan p) {
     for (int s = 0; s < KS; ++s)
       bk[kb][s] = as_bf16x8(key < n ? ld16(K + (int64_t)key * D + 32 * s + 8 * lg) : u32x4{0, 0, 0, 0});
   }
-  QT::issue(Qb, 0, R, qt0, w, lane);
+  uint32_t qoff[QT::kLoadsPerWave];
+#pragma unroll
+  for (int j = 0; j < QT::kLoadsPerWave; ++j) qoff[j] = QT::offset(j, w, lane, 63);
+  QT::issue_uniform(Qb, R, qoff, qt0, w, lane);
 
   // Row statistics: merge the key splits of pass 1.  Rows past R get a
   // reference of +inf so they contribute exp2(-inf) = 0.
@@ -485,7 +521,7 @@ __global__ __launch_bounds__(256, 3) void k_score_colsum(PrunePlan p) {
   const int ntiles = Rpad / 64;
   auto step = [&](auto par, int t) {
     constexpr int PAR = decltype(par)::value;
-    if (t + 1 < ntiles) QT::issue(Qb, (t + 1) * 64, R, PAR ? qt0 : qt1, w, lane);
+    if (t + 1 < ntiles) QT::issue_uniform(Qb + (int64_t)(t + 1) * 64 * D, R - (t + 1) * 64, qoff, PAR ? qt0 : qt1, w, lane);
     if (active) {
       const uint16_t *ql = PAR ? qt1 : qt0;
       // Two halves of two query blocks x four key blocks: eight accumulation

@@ -221,8 +221,8 @@ hipError_t launch_select(const PrunePlan &p, hipStream_t st) {
   if (grid == 0) return hipSuccess;
   // 256 threads hold up to 8 scores each, then 512 and 1024 threads up to 16,
   // then 1024 threads up to 32.  Fewer scores per thread shorten each radix
-  // pass; more waves lengthen the histogram scans, so 512 threads beat both
-  // 256 and 1024 at 3136 keys (measured).
+  // pass, more waves lengthen the barriers and the scan: 512 threads beat both
+  // 256 and 1024 at 3136 keys (measured with a histogram per wave).
   if (p.nmax <= 256 * 8)
     hipLaunchKernelGGL((k_select<256, 16>), dim3(grid), dim3(256), 0, st, p);
   else if (p.nmax <= 512 * 16)
