@@ -274,7 +274,7 @@ vc_status viscache_decode_attn(const vc_decode_shape *shape, const vc_cache *cac
                                size_t workspace_bytes, void *stream);
 
 /* Host only.  Workspace bytes viscache_decode_step needs (the decode
- * workspace plus one arrival counter per unit); 0 where
+ * workspace plus one word per unit); 0 where
  * viscache_decode_workspace_bytes is 0. */
 size_t viscache_decode_step_workspace_bytes(const vc_decode_shape *shape, int64_t max_rows);
 
@@ -287,7 +287,9 @@ size_t viscache_decode_step_workspace_bytes(const vc_decode_shape *shape, int64_
  * viscache_decode_step_workspace_bytes(shape, max_rows) bytes, 256-byte
  * aligned, zero-filled before its first use and not modified by the caller
  * between calls (the call leaves its counters at zero).  Calls sharing a
- * workspace must be ordered on one stream. */
+ * workspace must be ordered on one stream and agree in L*B*Hkv and d; their
+ * max_rows may differ (each needs the size for its own), and
+ * viscache_decode_attn calls may be among them. */
 vc_status viscache_decode_step(const vc_decode_shape *shape, const vc_cache *cache, const void *k_new,
                                const void *v_new, const void *q, float *out, float scale,
                                int64_t max_rows, void *workspace, size_t workspace_bytes, void *stream);
@@ -408,8 +410,8 @@ vc_status viscache_decode_plan(const vc_decode_shape *shape, const int32_t *cap,
  * plan_bytes at least viscache_decode_plan_bytes; a table built for another
  * shape or max_rows fills `out` with NaN.  The workspace is that of
  * viscache_decode_step (viscache_decode_step_workspace_bytes, zero-filled
- * before its first use, left at zero by every call); calls sharing it must be
- * ordered on one stream.  Every other argument and error as for
+ * before its first use, its counters left at zero by every call; sharing it
+ * with other calls as described there).  Every other argument and error as for
  * viscache_decode_step and viscache_decode_step_q4, plus VC_ERR_ARG for a
  * null or misaligned plan or a too small plan_bytes. */
 vc_status viscache_decode_step_planned(const vc_decode_shape *shape, const vc_cache *cache, const vc_qcache *qcache,

@@ -1015,7 +1015,9 @@ __global__ __launch_bounds__(256, 2) void k_decode_planned(DecodePlan p) {
   planned_body<D, Q4>(p);
 }
 
-// Merge the pieces of each split unit (second kernel of the two-call path).
+// Merge the pieces of each split unit (second kernel of the two-call path) and
+// clear the unit's table entry: the fused steps keep their arrival counters
+// there, zero between calls.
 template <int D>
 __global__ __launch_bounds__(256) void k_decode_combine(DecodePlan p) {
   const int u = blockIdx.x;
@@ -1023,6 +1025,8 @@ __global__ __launch_bounds__(256) void k_decode_combine(DecodePlan p) {
   const int np = ldg(reinterpret_cast<const int32_t *>(p.pinfo + u) + 1);
   __shared__ float2 mlb[128];
   if (np > 1) merge_pieces<D, false>(p, mlb, u, slot0, np);
+  __syncthreads();  // every thread has read the entry
+  if (threadIdx.x < 2) stg(reinterpret_cast<int32_t *>(p.pinfo + u) + threadIdx.x, 0);
 }
 
 }  // namespace

@@ -535,21 +535,24 @@ vc_status check_decode(const vc_decode_shape *s) {
   return VC_OK;
 }
 
-// Workspace layout of the decode calls: partial O and (max, sum) per piece
-// (workgroup), then the (first piece, pieces) table of the units; the fused
-// step adds one arrival counter per unit.
+// Workspace layout of the decode calls: a table of the units at the front,
+// then partial O and (max, sum) per piece (workgroup).  The two-call path
+// keeps each unit's (first piece, pieces) in the table, the fused steps their
+// arrival counters in its first half.  The counters are zero between calls, so
+// their place follows from the number of units alone, not from max_rows (as
+// the partials' extent does), and the two-call path leaves its table at zero.
+// (The step's size holds one more word per unit than it uses.)
 struct DecodeWs {
-  size_t o, ml, pinfo, arrive, base, step;
+  size_t table, o, ml, base, step;
 };
 DecodeWs decode_ws(int64_t units, int64_t nwg, int d) {
   const size_t slots = (size_t)nwg;
   DecodeWs w{};
-  w.o = 0;
-  w.ml = align_up(sizeof(float) * slots * 16 * (size_t)d);
-  w.pinfo = w.ml + align_up(sizeof(float2) * slots * 16);
-  w.arrive = w.pinfo + align_up(sizeof(int2) * (size_t)units);
-  w.base = w.arrive;
-  w.step = w.arrive + align_up(sizeof(uint32_t) * (size_t)units);
+  w.table = 0;
+  w.o = align_up(sizeof(int2) * (size_t)units);
+  w.ml = w.o + align_up(sizeof(float) * slots * 16 * (size_t)d);
+  w.base = w.ml + align_up(sizeof(float2) * slots * 16);
+  w.step = w.base + align_up(sizeof(uint32_t) * (size_t)units);
   return w;
 }
 
@@ -583,8 +586,8 @@ void decode_bind_ws(DecodePlan &p, uint8_t *ws) {
   const DecodeWs w = decode_ws(p.units, p.nwg, p.d);
   p.part_o = reinterpret_cast<float *>(ws + w.o);
   p.part_ml = reinterpret_cast<float2 *>(ws + w.ml);
-  p.pinfo = reinterpret_cast<int2 *>(ws + w.pinfo);
-  p.arrive = reinterpret_cast<uint32_t *>(ws + w.arrive);
+  p.pinfo = reinterpret_cast<int2 *>(ws + w.table);
+  p.arrive = reinterpret_cast<uint32_t *>(ws + w.table);
 }
 }  // namespace
 

@@ -142,7 +142,7 @@ struct DecodePlan {
   // [nwg][16][d] and [nwg][16] (max, sum).
   float *part_o;
   float2 *part_ml;
-  int2 *pinfo;       // [U] (first slot, pieces) of each unit (two-call path)
+  int2 *pinfo;       // [U] (first slot, pieces) of each unit (two-call path; zero once merged)
   // Fused step only: the row to append per unit ([U][d] each), the arrival
   // counters of the split units ([U], zero between calls) and the writable
   // views of pools and lengths.

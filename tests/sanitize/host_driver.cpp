@@ -19,6 +19,11 @@
 #include <vector>
 
 #include "../../include/viscache.h"
+#include "../../paper_2608_24063_amd/csrc/vc_internal.h"
+
+namespace vc {
+extern DecodePlan g_decode;  // launch_stubs.cpp
+}
 
 extern "C" {
 #include "../../oracle/oracle.h"
@@ -129,6 +134,39 @@ static int run_case(int idx, const std::vector<double> &v) {
     CHECK(viscache_decode_step(&ds, &c, fake(905), fake(906), fake(907), static_cast<float *>(fake(908)),
                                0.088f, max_rows, fake(909), dws - 1, nullptr) == VC_ERR_WORKSPACE,
           "case %d: decode short workspace", idx);
+    // Steps of one shape with different row bounds share a workspace: the
+    // arrival counters, zero between calls, lie where every step looks for
+    // them, whatever its bound, and no other step's partial results nor the
+    // two-call path's (which clears its table) reach them.
+    const int64_t nu = (int64_t)L * B * Hkv;
+    for (const int64_t mr : {max_rows, max_rows / 2, max_rows / 7, (int64_t)40}) {
+      const size_t need = viscache_decode_step_workspace_bytes(&ds, mr);
+      for (int planned = 0; planned < 2; ++planned) {
+        if (planned)
+          (void)viscache_decode_step_planned(&ds, &c, nullptr, fake(910), (size_t)1 << 30, fake(905), fake(906),
+                                             fake(907), static_cast<float *>(fake(908)), 0.088f, mr, fake(909), need,
+                                             nullptr);
+        else
+          (void)viscache_decode_step(&ds, &c, fake(905), fake(906), fake(907), static_cast<float *>(fake(908)), 0.088f,
+                                     mr, fake(909), need, nullptr);
+        const char *ctr = reinterpret_cast<const char *>(vc::g_decode.arrive);
+        CHECK(ctr == fake(909), "case %d: step counters at %td", idx, ctr - static_cast<char *>(fake(909)));
+        const char *po = reinterpret_cast<const char *>(vc::g_decode.part_o);
+        const char *ml = reinterpret_cast<const char *>(vc::g_decode.part_ml);
+        CHECK(po >= ctr + 4 * nu && ml >= po + (size_t)vc::g_decode.nwg * 16 * d * 4 &&
+                  ml + (size_t)vc::g_decode.nwg * 16 * 8 <= static_cast<char *>(fake(909)) + need,
+              "case %d: step partials", idx);
+      }
+      (void)viscache_decode_attn(&ds, &c, fake(907), static_cast<float *>(fake(908)), 0.088f, mr, fake(909),
+                                 viscache_decode_workspace_bytes(&ds, mr), nullptr);
+      const char *tb = reinterpret_cast<const char *>(vc::g_decode.pinfo);
+      const char *po = reinterpret_cast<const char *>(vc::g_decode.part_o);
+      const char *ml = reinterpret_cast<const char *>(vc::g_decode.part_ml);
+      CHECK(tb == fake(909) && po >= tb + 8 * nu && ml >= po + (size_t)vc::g_decode.nwg * 16 * d * 4 &&
+                ml + (size_t)vc::g_decode.nwg * 16 * 8 <=
+                    static_cast<char *>(fake(909)) + viscache_decode_workspace_bytes(&ds, mr),
+            "case %d: two-call table and partials", idx);
+    }
     // Allocation-free step: refused beyond its scratch, else it reaches the
     // (stub) scratch lookup.
     const bool fits = (int64_t)L * B * Hkv <= VC_DECODE_NOALLOC_UNITS &&

@@ -40,10 +40,15 @@ hipError_t launch_append(int32_t, int32_t, uint16_t *, uint16_t *, const int64_t
                          const uint16_t *, const uint16_t *, hipStream_t) {
   return hipErrorInvalidValue;
 }
-hipError_t launch_decode(const DecodePlan &p, hipStream_t) { return touch(&p, sizeof(p)); }
-hipError_t launch_decode_step(const DecodePlan &p, hipStream_t) { return touch(&p, sizeof(p)); }
-hipError_t launch_decode_step_q4(const DecodePlan &p, hipStream_t) { return touch(&p, sizeof(p)); }
-hipError_t launch_decode_planned(const DecodePlan &p, bool, hipStream_t) { return touch(&p, sizeof(p)); }
+DecodePlan g_decode;  // the plan of the last decode launch
+static hipError_t decode(const DecodePlan &p) {
+  g_decode = p;
+  return touch(&p, sizeof(p));
+}
+hipError_t launch_decode(const DecodePlan &p, hipStream_t) { return decode(p); }
+hipError_t launch_decode_step(const DecodePlan &p, hipStream_t) { return decode(p); }
+hipError_t launch_decode_step_q4(const DecodePlan &p, hipStream_t) { return decode(p); }
+hipError_t launch_decode_planned(const DecodePlan &p, bool, hipStream_t) { return decode(p); }
 hipError_t noalloc_scratch(uint8_t **out, hipStream_t) {
   *out = nullptr;
   return hipErrorInvalidValue;

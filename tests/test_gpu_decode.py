@@ -210,11 +210,12 @@ def test_decode_step_matches_append_then_attend(dev, orc, sg, d, Hq, Hkv):
 
 
 def _counters_zero(c, units):
-    """The fused step's arrival counters (after the decode workspace) are
-    back at zero."""
+    """The fused step's arrival counters (at the front of its workspace) are
+    back at zero, and the words past the decode workspace are untouched."""
     import paper_2608_24063_amd as vc
     base = vc.viscache_decode_workspace_bytes(c.shape, c.max_cap)
     assert int(c.step_ws[base:base + 4 * units].view(torch.int32).abs().sum()) == 0
+    assert int(c.step_ws[:4 * units].view(torch.int32).abs().sum()) == 0
 
 
 def test_decode_many_units_and_long_unit(dev, orc, sg):

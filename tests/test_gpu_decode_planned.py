@@ -56,6 +56,7 @@ def _counters_zero(c, units):
     import paper_2608_24063_amd as vc
     base = vc.viscache_decode_workspace_bytes(c.shape, c.max_cap)
     assert int(c.step_ws[base:base + 4 * units].view(torch.int32).abs().sum()) == 0
+    assert int(c.step_ws[:4 * units].view(torch.int32).abs().sum()) == 0  # the counters
 
 
 def _step_unplanned(c, kt, vt, qt, out, scale, max_rows):
@@ -263,3 +264,49 @@ def test_planned_table_mismatch(dev, sg):
                                         c.plan_rows, c.step_ws.data_ptr(), c.step_ws_bytes,
                                         torch.cuda.current_stream().cuda_stream)
     assert e.value.status == vc.VC_ERR_ARG
+
+
+@pytest.mark.parametrize("d,G", [(64, 2), (128, 7)])
+def test_calls_with_unlike_bounds_share_a_workspace(dev, d, G):
+    """Planned steps under a small row bound, device-cut steps under the
+    capacities, and the two-call path, in turn on one workspace: each finds its
+    arrival counters at zero although the extent of the partial results
+    differs.  Units in many pieces under either bound (lengths stay below the
+    small one).  The reference is the same step on another cache with a
+    workspace of its own; the pieces differ with the bound, so results agree to
+    fp32 rounding (weights as bf16 pairs, within 2^-17)."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import DecodeCache
+    L, B, Hkv, bound = 2, 2, 2, 1500
+    units = L * B * Hkv
+    lens = [1400, 30, 700, 1200, 0, 1450, 333, 64]
+    caps = [n + 40 + (4000 if u % 2 else 0) for u, n in enumerate(lens)]
+    a, b = (DecodeCache(L, B, Hkv * G, Hkv, d, caps, dev) for _ in range(2))
+    gen = torch.Generator(device=dev).manual_seed(d)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev).to(torch.bfloat16)
+    for x in (a, b):
+        x.len.copy_(torch.tensor(lens, dtype=torch.int32))
+    a.k_pool.copy_(rnd(*a.k_pool.shape))
+    a.v_pool.copy_(rnd(*a.v_pool.shape))
+    b.k_pool.copy_(a.k_pool)
+    b.v_pool.copy_(a.v_pool)
+    a.plan(bound)
+    assert (vc.viscache_decode_workspace_bytes(a.shape, bound) < vc.viscache_decode_workspace_bytes(a.shape, a.max_cap))
+    assert a.ws_bytes <= a.step_ws_bytes
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def two_calls(k, v, q, o, s):
+        a.append(k, v)
+        vc.viscache_decode_attn(a.shape, a.c, q.data_ptr(), o.data_ptr(), s, a.max_cap, a.step_ws.data_ptr(),
+                                a.ws_bytes, stream)
+
+    for t in range(9):
+        k, v, q = rnd(L, B, Hkv, d), rnd(L, B, Hkv, d), rnd(L, B, Hkv * G, d)
+        oa, ob = (torch.full((L, B, Hkv * G, d), float("nan"), device=dev) for _ in range(2))
+        (a.step_planned, a.step, two_calls)[t % 3](k, v, q, oa, d ** -0.5)
+        b.step(k, v, q, ob, d ** -0.5)
+        torch.cuda.synchronize()
+        assert a.len.cpu().tolist() == b.len.cpu().tolist() == [n + t + 1 for n in lens], f"step {t}"
+        assert float((oa - ob).abs().max()) <= 2.0 ** -16 * float(a.v_pool.float().abs().max()), f"step {t}"
+        _counters_zero(a, units)
+    assert _bits_equal(a.k_pool, b.k_pool) and _bits_equal(a.v_pool, b.v_pool)
