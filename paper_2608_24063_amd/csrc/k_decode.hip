@@ -356,20 +356,39 @@ __device__ __forceinline__ Piece cut_groups(const DecodePlan &p, uint32_t i) {
       for (int q = 0; q < NQ; ++q) P[q] += wave_sum(v[q]);
     }
   };
-  // The first bound fits for most caches; the others are tried only if not.
-  // (All four at once, over the four groups of a larger call, took a layer's
-  // step of 4 units and 500 to 1300 rows from 11.0 to 12.0 us.)
-  uint32_t cb = c0;
-  uint32_t P0[1];
-  count(0, P0);
-  if (P0[0] > N) {  // uniform
+  // Where none of the four fits.
+  auto most = [&]() {
     const uint32_t free_ = N - (uint32_t)p.units;
-    cb = ((T / free_ + (T % free_ != 0)) + 3u) & ~3u;
-    uint32_t P[3];
-    count(1, P);
+    return ((T / free_ + (T % free_ != 0)) + 3u) & ~3u;
+  };
+  // The first bound fits for most caches of few units, and counting it alone
+  // is shorter (all four at once, over the four groups of a larger call, took a
+  // layer's step of 4 units and 500 to 1300 rows from 11.0 to 12.0 us); the
+  // others follow if it does not fit.  With more than one chunk that is another
+  // pass over the tables, so all four are counted at once where the first is
+  // not expected to fit: a unit's last piece is half full on average.  (Steps
+  // over 1920 units of 200 to 1700 rows: 204 us at once, 216 in two passes; 896
+  // units of 250 to 1500 rows: 68 and 71; 336 units of 65 to 1900 rows, whose
+  // first bound fits: 35.0 and 31.8.)
+  uint32_t cb = c0;
+  if (nch == 1 || T + (uint64_t)c0 * (uint32_t)p.units / 2 <= (uint64_t)(N + N / 16) * c0) {  // uniform
+    uint32_t P0[1];
+    count(0, P0);
+    if (P0[0] > N) {  // uniform
+      uint32_t P[3];
+      count(1, P);
+      cb = most();
 #pragma unroll
-    for (int q = 2; q >= 0; --q)
-      if (P[q] <= N) cb = c0 + 4u * (q + 1);
+      for (int q = 2; q >= 0; --q)
+        if (P[q] <= N) cb = c0 + 4u * (q + 1);
+    }
+  } else {
+    uint32_t P[4];
+    count(0, P);
+    cb = most();
+#pragma unroll
+    for (int q = 3; q >= 0; --q)
+      if (P[q] <= N) cb = c0 + 4u * q;
   }
   const bool small_b = T + cb < (1u << 20);
   const Recip rcb = recip(cb, small_b);

@@ -306,3 +306,35 @@ def test_step_layers_with_unlike_capacities(dev, sg, d, Hkv):
         assert float((oa - ob).abs().max()) <= 2.0 ** -16 * float(a.v_pool.float().abs().max())
         assert torch.equal(a.len, b.len) and a.len.cpu().tolist() == (lens + t + 1).tolist()
     assert torch.equal(a.k_pool, b.k_pool) and torch.equal(a.v_pool, b.v_pool)
+
+
+@pytest.mark.parametrize("units,lo,hi", [(130, 100, 900), (130, 770, 780), (300, 100, 900), (300, 513, 514),
+                                         (300, 300, 600), (300, 1025, 1030), (700, 100, 300), (700, 100, 900),
+                                         (700, 40, 2500)])
+def test_cut_of_many_units(dev, units, lo, hi):
+    """The device's cut with one chunk of units and with several: the smallest
+    piece bound fits, a larger one does (found after the first or with it), or
+    none of the four.  Against the planned step, whose pieces are cut on the
+    host: equal to fp32 rounding (weights as bf16 pairs, within 2^-17)."""
+    import random
+    from paper_2608_24063_amd.tensors import DecodeCache
+    rng, d = random.Random(units), 64
+    caps = [rng.randint(lo, hi) for _ in range(units)]
+    a, b = (DecodeCache(1, 1, units, units, d, caps, dev) for _ in range(2))
+    gen = torch.Generator(device=dev).manual_seed(units)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev).to(torch.bfloat16)
+    lens = torch.tensor([c - rng.randint(1, 30) for c in caps], dtype=torch.int32)
+    a.k_pool.copy_(rnd(*a.k_pool.shape))
+    a.v_pool.copy_(rnd(*a.v_pool.shape))
+    b.k_pool.copy_(a.k_pool)
+    b.v_pool.copy_(a.v_pool)
+    for x in (a, b):
+        x.len.copy_(lens)
+    b.plan()
+    k, v, q = rnd(1, 1, units, d), rnd(1, 1, units, d), rnd(1, 1, units, d)
+    oa, ob = (torch.full((1, 1, units, d), float("nan"), device=dev) for _ in range(2))
+    a.step(k, v, q, oa, d ** -0.5)
+    b.step_planned(k, v, q, ob, d ** -0.5)
+    torch.cuda.synchronize()
+    assert a.len.cpu().tolist() == b.len.cpu().tolist() == [int(n) + 1 for n in lens]
+    assert float((oa - ob).abs().max()) <= 2.0 ** -16 * float(a.v_pool.float().abs().max())
