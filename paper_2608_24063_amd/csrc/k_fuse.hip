@@ -51,13 +51,8 @@ namespace {
 constexpr float kNegInf = -__builtin_inff();
 // A probability against a stale maximum may reach 2^kGrowLimit before the
 // maximum is raised: fp32 keeps the accumulators finite (at most 2^15 dropped
-// rows of values below 2^16 in magnitude).
+// rows of values below 2^80 in magnitude).
 constexpr float kGrowLimit = 32.f;
-// Probabilities below 2^-kSkipBits of a row's largest are not worth adding:
-// the denominator is at least the largest, so each of them is lost in its
-// rounding, and all 2^15 dropped rows together are below 2^-33 of it.
-constexpr float kSkipBits = 48.f;
-
 // Staged dropped tile: rows of D bf16 at a pitch of D + 16 elements.  On
 // gfx950 (LDS serves 64 banks x 4 bytes per pass) this pitch keeps all three
 // access patterns below conflict-free at full rate (measured): 16-byte writes
@@ -89,6 +84,17 @@ __device__ __forceinline__ T *boff(uint64_t base, uint32_t off) {
   return reinterpret_cast<T *>(base + off);
 }
 
+// The squares of eight bf16 values added up in two sums.
+__device__ __forceinline__ void add_squares(u32x4 v, float (&s)[2]) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t u = v[i];  // (a bit cast of v[i] itself takes element 0)
+    const bf16x2 x = __builtin_bit_cast(bf16x2, u);
+    s[i & 1] = __builtin_amdgcn_fdot2_f32_bf16(x, x, s[i & 1], false);
+  }
+}
+
 // Rows of one 64-row dropped tile between their global load and their LDS
 // store: thread t owns 16-byte chunk t % kCpr of rows t / kCpr + kRpp * it,
 // so every 16 lanes move whole rows (coalesced in HBM, conflict-free in LDS).
@@ -106,6 +112,13 @@ struct DropRegs {
     constexpr int PR = kPitchRow<D>;
 #pragma unroll
     for (int it = 0; it < kIt; ++it) *reinterpret_cast<u32x4 *>(vr + (row0 + kRpp * it) * PR + chunk * 8) = v[it];
+  }
+  // Some value's square may reach the bound, or is not a number.
+  __device__ __forceinline__ bool large(float bound) const {
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) add_squares(v[it], s);
+    return !(s[0] + s[1] < bound);
   }
 };
 
@@ -231,9 +244,10 @@ __device__ __forceinline__ void values_half(FuseState<D> &st, const uint16_t *vt
 
 // One 64-row dropped tile (nd valid rows).  A wave whose every logit of a
 // half lies more than kSkipBits below its row's running max passes over the
-// half: each probability is below 2^-kSkipBits of the row's denominator.
+// half (vc_internal.h), unless hold is +inf (else -inf).
 template <int D, bool VFP32, bool MASK>
-__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, int nd, float tc, int lr, int lg) {
+__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, float hold, int nd, float tc, int lr,
+                                          int lg) {
   f32x4 accA[2][2], accB[2][2];
   bf16x8 phA[2], plA[2], phB[2], plB[2];
   float mxA[2], mxB[2];
@@ -242,7 +256,7 @@ __device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, 
   half_max<MASK>(accA, 0, nd, tc, lg, mxA);
   half_max<MASK>(accB, 1, nd, tc, lg, mxB);
   auto far = [&](const float (&mx)[2]) {  // wave-uniform
-    return __builtin_amdgcn_ballot_w64(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]) > -kSkipBits) == 0;
+    return __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]), hold) > -kSkipBits) == 0;
   };
   const bool fa = far(mxA), fb = far(mxB);
   if (!fa) {
@@ -267,7 +281,7 @@ using DropTiles = uint16_t[2][kDropTile * kPitchRow<D>];
 // starts fetching the next job's record while this one blends and stores).
 template <int D, bool VFP32, typename Next>
 __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[4], int tile, int start, DropTiles<D> &vr,
-                                         Next &&next) {
+                                         float &s_hold, Next &&next) {
   constexpr int KS = D / 32, MB = D / 16, NB = 2;
   constexpr uint32_t kRowBytes = D * 2;
   const uint64_t Kin = uni64(rec[0].x, rec[0].y), Vin = uni64(rec[0].z, rec[0].w);
@@ -357,9 +371,15 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   }
   // The previous job's waves may still read their kept values from the
   // tile buffers (below): nothing is staged before every wave is past them.
+  if (tid == 0) s_hold = kNegInf;
   __syncthreads();
+  // Once a staged value is too large, no later tile is passed over.
+  auto check = [&](const Regs &set) {
+    if (__builtin_amdgcn_ballot_w64(set.large(p.skip_sq)) != 0) s_hold = -kNegInf;
+  };
   if (ntiles > 0) {
     set0.store(vr[0], row0, chunk);
+    check(set0);
     int rr[kIt];
     clamp_rows(di[2], rr);
     set0.load(Vin, rr, chunk);
@@ -400,6 +420,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
     constexpr int PAR = decltype(par)::value;
     Regs &nx = PAR ? set0 : set1;
     nx.store(vr[PAR ^ 1], row0, chunk);
+    check(nx);
     int nxt[kIt], rr[kIt];
     raw_idx(t + 4, nxt);
     clamp_rows(pend, rr);
@@ -412,19 +433,19 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   using P1 = std::integral_constant<int, 1>;
   int t = 0;
   for (; t + 1 < nfull; t += 2) {
-    fuse_tile<D, VFP32, false>(st, vr[0], kDropTile, tc, lr, lg);
+    fuse_tile<D, VFP32, false>(st, vr[0], s_hold, kDropTile, tc, lr, lg);
     advance(P0{}, t);
-    fuse_tile<D, VFP32, false>(st, vr[1], kDropTile, tc, lr, lg);
+    fuse_tile<D, VFP32, false>(st, vr[1], s_hold, kDropTile, tc, lr, lg);
     advance(P1{}, t + 1);
   }
   if (t < nfull) {
-    fuse_tile<D, VFP32, false>(st, vr[0], kDropTile, tc, lr, lg);
+    fuse_tile<D, VFP32, false>(st, vr[0], s_hold, kDropTile, tc, lr, lg);
     advance(P0{}, t);
     ++t;
   }
   if (t < ntiles) {  // partial last tile
     const int nd = r - t * kDropTile;
-    fuse_tile<D, VFP32, true>(st, vr[t & 1], nd, tc, lr, lg);
+    fuse_tile<D, VFP32, true>(st, vr[t & 1], s_hold, nd, tc, lr, lg);
   }
   next();
 
@@ -484,6 +505,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
 template <int D, bool VFP32>
 __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
   __shared__ __attribute__((aligned(16))) DropTiles<D> vr;
+  __shared__ float s_hold;
   __shared__ int s_code;
   const int x = (int)(blockIdx.x % kXcds);
   const int q0 = ldg(p.fwoff + x), qlen = ldg(p.fwoff + x + 1) - q0;
@@ -511,7 +533,7 @@ __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
     int ncode = -1;
     u32x4 nrec[4] = {};
     int nstart = 0;
-    fuse_job<D, VFP32>(p, rec, code & 255, (int)uni((uint32_t)start), vr, [&]() {
+    fuse_job<D, VFP32>(p, rec, code & 255, (int)uni((uint32_t)start), vr, s_hold, [&]() {
       ncode = take();
       if (ncode >= 0) fetch(ncode, nrec, nstart);
     });

@@ -470,6 +470,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   pl.sc = (float)(1.4426950408889634 / std::sqrt((double)y.d));
   pl.tc = (float)(1.4426950408889634 / (double)params->tau);
   pl.mu = params->mu;
+  pl.skip_sq = fuse_skip_sq(params->tau, params->mu, y.d);
   pl.Ntot = y.Ntot;
   pl.w_lp = (int32_t)(y.p_lp / 4);
   pl.w_toff = (int32_t)(y.p_toff / 4);

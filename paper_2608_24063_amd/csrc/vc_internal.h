@@ -5,6 +5,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 namespace vc {
 
 // Indices into the per-layer pointer table.
@@ -22,6 +25,27 @@ constexpr int kSelectThreads = 1024;
 constexpr int kSelectPerThread = 32;  // => n <= 32768 tokens per sequence
 constexpr int kMaxTokens = kSelectThreads * kSelectPerThread;
 constexpr int kXcdsHost = 8;      // MI355X accelerator dies (host-side grid planning)
+
+// Fusion leaves out a dropped row whose logit lies kSkipBits (in log2) or more
+// below a row's running maximum, where nothing it would add survives rounding.
+//   The denominator is at least 1 (in units of the maximum's weight), the 2^15
+// dropped rows at most are together below 2^(15 - kSkipBits) of it.
+//   The values: with every |V_d| <= M, they would add (1 - mu) 2^(15 -
+// kSkipBits) M at most, which is below 2^-24 mu |V_k| (lost in the rounding of
+// mu V_k) if M is not too large against |V_k|.  That needs no look at V_k: the
+// two logits differ by kSkipBits ln 2 tau at least, and by 2 |V_k| sqrt(d) M at
+// most, so |V_k| >= kSkipBits ln 2 tau / (2 sqrt(d) M).  Rows are therefore left
+// out while every square of a dropped value is below
+//   skip_sq = 2^(kSkipBits - 39) kSkipBits ln 2 tau / (2 sqrt(d)) mu / (1 - mu)
+// (with tau = 1, mu = 0.7, d = 128: |V_d| up to 720; 48 bits would allow 42).
+// Larger values, and such that are not finite, keep every row.
+constexpr int kSkipBits = 56;
+inline float fuse_skip_sq(double tau, double mu, int d) {
+  const double margin = (double)(int64_t(1) << (kSkipBits - 39));
+  const double s = mu < 1.0 ? margin * (kSkipBits * 0.6931471805599453 * tau / (2.0 * std::sqrt((double)d))) * mu / (1.0 - mu)
+                            : 1e37;
+  return (float)std::min(s, 1e37);
+}
 
 // One fusion unit (layer, sequence, kv head) with kept rows, as the fusion
 // kernel reads it: absolute addresses of the unit's first rows and its sizes.
@@ -63,6 +87,7 @@ struct PrunePlan {
   float sc;           // log2(e) / sqrt(d)
   float tc;           // log2(e) / tau
   float mu;
+  float skip_sq;      // fusion passes over tiles whose squared values are below this (kSkipBits)
   int64_t Ntot;       // sum_b n_b
   int32_t w_lp, w_toff, w_nb;  // word offsets of those tables in the plan (first chunk)
   const uint64_t *lp;   // [LP_COUNT][L] per-layer device pointers

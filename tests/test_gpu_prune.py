@@ -285,6 +285,45 @@ def test_fusion_passes_over_far_tiles(dev, orc, d, values):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("near,far,mu", [(6.0, 2.0 ** 40, 0.7), (8.0, 2.0 ** 100, 0.7), (6.0, 2.0 ** 40, 0.0),
+                                         (6.0, 2.0 ** 7, 0.7), (6.0, 2.0 ** -40, 1.0)])
+@pytest.mark.parametrize("vfp32", [True, False])
+def test_fusion_keeps_large_values_of_small_weight(dev, orc, d, near, far, mu, vfp32):
+    """Dropped rows far below a row's running max (their weights are 2^-52 or
+    2^-92 of it) whose values, in a column where the others have none, are so
+    large that they still make that column of the result: they are not passed
+    over.  Also of sizes at which they may be.  A column's terms have one sign,
+    so it is within the weights' rounding (a bf16 pair's 2^-17 or a bf16's 2^-9)
+    and the output's of the oracle's; where passing over is allowed, what is
+    left out is below 2^-24 mu |V_k|."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    from synthgen.device import to_host_bf16
+    gen = np.random.default_rng(3)
+    n, L = 1000, 2
+    params = vc.make_params(0.25, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, drop_all=True, v_out_fp32=vfp32, mu=mu)
+    V = np.zeros((n, d), np.float32)
+    V[: n // 2, 0] = near
+    V[n // 2:, d - 1] = far
+    K = 0.1 * gen.standard_normal((n, d)).astype(np.float32)
+    K[: n // 4, 0] += 4.0  # the kept tokens: the first quarter
+    Q = np.zeros((1, 1, 4, d), np.float32)
+    Q[..., 0] = 8.0
+    mk = lambda x: torch.from_numpy(x).to(torch.bfloat16).to(dev)
+    Vt, Kt = [mk(V)] * L, [mk(K)] * L
+    pc = PruneCall(1, L, 1, 1, d, 4, [n], params, Kt, Vt, [torch.from_numpy(Q).to(dev)] * L, with_drop=True)
+    pc.run()
+    torch.cuda.synchronize()
+    for l in range(L):
+        kept, drop = pc.idx_out[l].cpu().numpy(), pc.drop_out[l].cpu().numpy()
+        assert kept.max() < n // 2 and (drop >= n // 2).sum() == n // 2
+        ref = orc.fuse(to_host_bf16(Vt[l]), kept, drop, 1.0, mu)
+        got = pc.v_out[l].float().cpu().numpy().astype(np.float64)
+        bound = (2.0 ** -16 if vfp32 else 2.0 ** -7) * np.abs(ref) + (2.0 ** -24 * mu * near if far < 2.0 ** 10 else 0)
+        assert (np.abs(got - ref) <= bound).all(), np.abs(got - ref).max(0)[[0, d - 1]]
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("G,W", [(1, 1), (1, 17), (3, 16), (5, 13), (7, 64), (16, 16), (1, 257), (16, 64)])
 def test_window_scores_over_row_and_tile_counts(dev, orc, d, G, W):
     """Window scores of every token at row counts around the 16-row block, the
