@@ -244,9 +244,9 @@ __device__ __forceinline__ void values_half(FuseState<D> &st, const uint16_t *vt
 
 // One 64-row dropped tile (nd valid rows).  A wave whose every logit of a
 // half lies more than kSkipBits below its row's running max passes over the
-// half (vc_internal.h), unless hold is +inf (else -inf).
+// half (vc_internal.h), unless `hold` (uniform) keeps every row.
 template <int D, bool VFP32, bool MASK>
-__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, float hold, int nd, float tc, int lr,
+__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, bool hold, int nd, float tc, int lr,
                                           int lg) {
   f32x4 accA[2][2], accB[2][2];
   bf16x8 phA[2], plA[2], phB[2], plB[2];
@@ -256,7 +256,7 @@ __device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, 
   half_max<MASK>(accA, 0, nd, tc, lg, mxA);
   half_max<MASK>(accB, 1, nd, tc, lg, mxB);
   auto far = [&](const float (&mx)[2]) {  // wave-uniform
-    return __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]), hold) > -kSkipBits) == 0;
+    return !hold && __builtin_amdgcn_ballot_w64(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]) > -kSkipBits) == 0;
   };
   const bool fa = far(mxA), fb = far(mxB);
   if (!fa) {
@@ -281,7 +281,7 @@ using DropTiles = uint16_t[2][kDropTile * kPitchRow<D>];
 // starts fetching the next job's record while this one blends and stores).
 template <int D, bool VFP32, typename Next>
 __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[4], int tile, int start, DropTiles<D> &vr,
-                                         float &s_hold, Next &&next) {
+                                         int (&s_hold)[2], Next &&next) {
   constexpr int KS = D / 32, MB = D / 16, NB = 2;
   constexpr uint32_t kRowBytes = D * 2;
   const uint64_t Kin = uni64(rec[0].x, rec[0].y), Vin = uni64(rec[0].z, rec[0].w);
@@ -371,15 +371,19 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   }
   // The previous job's waves may still read their kept values from the
   // tile buffers (below): nothing is staged before every wave is past them.
-  if (tid == 0) s_hold = kNegInf;
+  if (tid < 2) s_hold[tid] = 0;
   __syncthreads();
-  // Once a staged value is too large, no later tile is passed over.
-  auto check = [&](const Regs &set) {
-    if (__builtin_amdgcn_ballot_w64(set.large(p.skip_sq)) != 0) s_hold = -kNegInf;
+  // From the first tile with a too large value on, no tile is passed over.  A
+  // staged tile's word belongs to its buffer: it is written before the barrier
+  // that the tile's readers are past and again only after the next, so every
+  // wave, and every run, decides alike.
+  bool hold = false;
+  auto check = [&](const Regs &set, int buf) {
+    if (__builtin_amdgcn_ballot_w64(set.large(p.skip_sq)) != 0) s_hold[buf] = 1;
   };
   if (ntiles > 0) {
     set0.store(vr[0], row0, chunk);
-    check(set0);
+    check(set0, 0);
     int rr[kIt];
     clamp_rows(di[2], rr);
     set0.load(Vin, rr, chunk);
@@ -420,7 +424,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
     constexpr int PAR = decltype(par)::value;
     Regs &nx = PAR ? set0 : set1;
     nx.store(vr[PAR ^ 1], row0, chunk);
-    check(nx);
+    check(nx, PAR ^ 1);
     int nxt[kIt], rr[kIt];
     raw_idx(t + 4, nxt);
     clamp_rows(pend, rr);
@@ -431,21 +435,25 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   };
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
+  auto tile_of = [&](auto mask, int buf, int nd) {
+    hold |= uni((uint32_t)s_hold[buf]) != 0;
+    fuse_tile<D, VFP32, decltype(mask)::value>(st, vr[buf], hold, nd, tc, lr, lg);
+  };
   int t = 0;
   for (; t + 1 < nfull; t += 2) {
-    fuse_tile<D, VFP32, false>(st, vr[0], s_hold, kDropTile, tc, lr, lg);
+    tile_of(std::false_type{}, 0, kDropTile);
     advance(P0{}, t);
-    fuse_tile<D, VFP32, false>(st, vr[1], s_hold, kDropTile, tc, lr, lg);
+    tile_of(std::false_type{}, 1, kDropTile);
     advance(P1{}, t + 1);
   }
   if (t < nfull) {
-    fuse_tile<D, VFP32, false>(st, vr[0], s_hold, kDropTile, tc, lr, lg);
+    tile_of(std::false_type{}, 0, kDropTile);
     advance(P0{}, t);
     ++t;
   }
   if (t < ntiles) {  // partial last tile
     const int nd = r - t * kDropTile;
-    fuse_tile<D, VFP32, true>(st, vr[t & 1], s_hold, nd, tc, lr, lg);
+    tile_of(std::true_type{}, t & 1, nd);
   }
   next();
 
@@ -505,7 +513,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
 template <int D, bool VFP32>
 __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
   __shared__ __attribute__((aligned(16))) DropTiles<D> vr;
-  __shared__ float s_hold;
+  __shared__ int s_hold[2];
   __shared__ int s_code;
   const int x = (int)(blockIdx.x % kXcds);
   const int q0 = ldg(p.fwoff + x), qlen = ldg(p.fwoff + x + 1) - q0;

@@ -324,6 +324,40 @@ def test_fusion_keeps_large_values_of_small_weight(dev, orc, d, near, far, mu, v
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("vfp32", [True, False])
+def test_fusion_repeats_bitwise_around_large_values(dev, d, vfp32):
+    """Tiles far below the running max are passed over until a tile with too
+    large a value is met.  Which tiles that are does not depend on how the
+    waves of a workgroup run against each other: many jobs with a large value
+    in some middle tile give the same bits every time."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    gen = torch.Generator(device=dev).manual_seed(d)
+    L, B, n, Hkv, tpf = 2, 2, 3000, 4, 50
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev)
+    params = vc.make_params(0.4, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, drop_all=True, v_out_fp32=vfp32)
+    K, V, Q = [], [], []
+    for l in range(L):
+        f = torch.arange(n, device=dev) // tpf
+        v = 2.0 * (0.8 * rnd(B, Hkv, n // tpf, d)[:, :, f] + 0.6 * rnd(B, Hkv, n, d))
+        for b in range(B):
+            for g in range(Hkv):
+                v[b, g, 300 * (2 * b + g) + 450, g] = 2.0 ** (11 + g)
+        V.append(v.bfloat16().view(-1, d))
+        K.append(rnd(B * Hkv * n, d).bfloat16())
+        Q.append(rnd(B, Hkv, 4, d))
+    first = None
+    for _ in range(6):
+        pc = PruneCall(B, L, Hkv, Hkv, d, 4, [n] * B, params, K, V, Q)
+        pc.run()
+        torch.cuda.synchronize()
+        got = [o.clone() for o in pc.v_out]
+        assert all(bool(torch.isfinite(o).all()) for o in got)
+        first = first or got
+        assert all(torch.equal(x, y) for x, y in zip(first, got))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("G,W", [(1, 1), (1, 17), (3, 16), (5, 13), (7, 64), (16, 16), (1, 257), (16, 64)])
 def test_window_scores_over_row_and_tile_counts(dev, orc, d, G, W):
     """Window scores of every token at row counts around the 16-row block, the
