@@ -21,24 +21,26 @@
 // into one of two LDS buffers one tile ahead.  A tile is processed as two
 // halves of 32 dropped rows, which are the two k-steps of the second product.
 // The running row maximum is lazy: a half's probabilities are taken against
-// the maximum as it stands, and only when a logit lies more than 2^32 above
-// it (always on a job's first half) is the maximum raised and the
-// accumulators rescaled.
+// the maximum as it stands, and only when a logit lies far above it (32 in log2
+// where halves are passed over, 64 elsewhere; always on a job's first half) is
+// the maximum raised and the accumulators rescaled.
 //
 // Values of one frame resemble each other and the logits carry no 1/sqrt(d),
 // so a kept row's softmax is concentrated on the dropped rows of a few frames.
 // A wave passes over the exponentials and value products of a half whose
-// logits all lie 48 (in log2) below its rows' running maxima, where nothing
-// they would add survives rounding, and the tiles are walked from beside the
-// job's own place in the sequence, so that the maxima are high from the first
-// tiles on.  Measured on eight sequences of 14k to 23k tokens (28 layers, 4 kv
-// heads, d = 128): 2.59 -> 1.91 ms, with 42% of the value products left when
-// whole tiles were passed over from an estimated start (2.03 ms) and fewer by
-// halves from the exact one; 12.5k tokens: 169 -> 138 us.  What is left there
-// is the score products (0.50 ms, at the matrix cores' rate), staging
-// (0.35 ms) and the jobs' row copies (0.77 ms, at the rate of a large copy),
-// which overlap little.  On values without frames nothing is passed over and
-// the test costs 5% (167 -> 175 us).
+// logits all lie kSkipBits (in log2) below its rows' running maxima, where
+// nothing they would add survives rounding, and the tiles are walked from
+// beside the job's own place in the sequence, so that the maxima are high from
+// the first tiles on.  That needs the half's largest logits before its
+// exponentials, which then overlap less with the products, and a look at the
+// sizes of the values; so a job whose waves do not pass over enough goes on
+// without.  Fusion of eight sequences of 14k to 23k tokens (28 layers, 4 kv
+// heads, d = 128), in us: never looking 2480 with values in frames and without;
+// always 1980 and 2850; as it is 2030 and 2650.  12.5k tokens: 168 and 163;
+// 141 and 176; 143 and 170.  (Of the 2030, the score products take 500, at the
+// matrix cores' rate, staging 350 and the jobs' row copies 770, at the rate of
+// a large copy; they overlap little.)  A job that could start to look again
+// gained nothing (2100 and 2700).
 #include <type_traits>
 
 #include "vc_device.h"
@@ -49,10 +51,20 @@ namespace vc {
 namespace {
 
 constexpr float kNegInf = -__builtin_inff();
-// A probability against a stale maximum may reach 2^kGrowLimit before the
-// maximum is raised: fp32 keeps the accumulators finite (at most 2^15 dropped
-// rows of values below 2^80 in magnitude).
-constexpr float kGrowLimit = 32.f;
+// A probability against a stale maximum may reach 2^kGrowBits, or a lane's sum
+// of a half tile kGrowSum, before the maximum is raised: fp32 keeps the
+// accumulators finite (at most 2^15 dropped rows of values below 2^48 in
+// magnitude).  The smaller one keeps the running maxima, which tell what is
+// far, close to the true ones; with it the tiles that pass over nothing take
+// 3.5% longer.
+constexpr float kGrowBits = 32.f;
+constexpr float kGrowSum = 0x1p64f;
+// A job of at least kFarTiles full tiles looks for halves to pass over, for as
+// long as its four waves have passed over more than kFarEach halves a tile (of
+// eight), less kFarStart: looking costs what one or two halves do.  With 4 for
+// kFarStart jobs gave up too early on values in frames (2160 us of fusion), with
+// 16 too late on others (2710).
+constexpr int kFarTiles = 3, kFarEach = 2, kFarStart = 8;
 // Staged dropped tile: rows of D bf16 at a pitch of D + 16 elements.  On
 // gfx950 (LDS serves 64 banks x 4 bytes per pass) this pitch keeps all three
 // access patterns below conflict-free at full rate (measured): 16-byte writes
@@ -113,12 +125,12 @@ struct DropRegs {
 #pragma unroll
     for (int it = 0; it < kIt; ++it) *reinterpret_cast<u32x4 *>(vr + (row0 + kRpp * it) * PR + chunk * 8) = v[it];
   }
-  // Some value's square may reach the bound, or is not a number.
-  __device__ __forceinline__ bool large(float bound) const {
+  // The sum of the values' squares.
+  __device__ __forceinline__ float squares() const {
     float s[2] = {0.f, 0.f};
 #pragma unroll
     for (int it = 0; it < kIt; ++it) add_squares(v[it], s);
-    return !(s[0] + s[1] < bound);
+    return s[0] + s[1];
   }
 };
 
@@ -151,18 +163,10 @@ __device__ __forceinline__ void scores_half(const FuseState<D> &st, const uint16
 }
 
 // Each lane's largest logit of a half tile per kept block, scaled by
-// log2(e)/tau.  MASK: rows at or past nd are not dropped rows.
-template <bool MASK>
-__device__ __forceinline__ void half_max(f32x4 (&acc)[2][2], int h, int nd, float tc, int lg, float (&mx)[2]) {
+// log2(e)/tau.
+__device__ __forceinline__ void half_max(const f32x4 (&acc)[2][2], float tc, float (&mx)[2]) {
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
-    if (MASK) {
-#pragma unroll
-      for (int d2 = 0; d2 < 2; ++d2)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (32 * h + 16 * d2 + 4 * lg + i >= nd) acc[nb][d2][i] = kNegInf;
-    }
     float m = acc[nb][0][0];
 #pragma unroll
     for (int j = 1; j < 8; ++j) m = fmaxf(m, acc[nb][j / 4][j % 4]);
@@ -170,44 +174,63 @@ __device__ __forceinline__ void half_max(f32x4 (&acc)[2][2], int h, int nd, floa
   }
 }
 
-// Online softmax of one half tile: the running max raised if some logit is
-// far above it (mx: the lane's largest, half_max), then probabilities against
-// it, the denominators, and the bf16 B operands of O^T (with VFP32, also the
-// low parts).
-template <int D, bool VFP32>
-__device__ __forceinline__ void softmax_half(FuseState<D> &st, const f32x4 (&acc)[2][2], const float (&mx)[2],
-                                             float tc, bf16x8 (&ph)[2], bf16x8 (&pl)[2]) {
-  constexpr int MB = D / 16;
-  if (__builtin_amdgcn_ballot_w64(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]) > kGrowLimit) != 0) {
-    // Raise each kept row's max to cover this half (the four lane groups of
-    // a row agree on it) and rescale what is accumulated.
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      float m = fmaxf(mx[nb], shfl_xor(mx[nb], 16));
-      m = fmaxf(m, shfl_xor(m, 32));
-      const float mc = fmaxf(st.mrow[nb], m);
-      const float alpha = fast_exp2(st.mrow[nb] - mc);
-      st.mrow[nb] = mc;
-      st.lsum[nb] *= alpha;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) st.O[nb][mb] *= alpha;
-    }
-  }
-  float pr[2][2][4];
+// Raises each kept row's running max to cover a half tile (mx: the lane's
+// largest scaled logits; the four lane groups of a row agree on it) and
+// rescales what is accumulated.
+template <int D>
+__device__ __forceinline__ void raise_max(FuseState<D> &st, const float (&mx)[2]) {
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
-    float part = 0.f;
+    float m = fmaxf(mx[nb], shfl_xor(mx[nb], 16));
+    m = fmaxf(m, shfl_xor(m, 32));
+    const float mc = fmaxf(st.mrow[nb], m);
+    const float alpha = fast_exp2(st.mrow[nb] - mc);
+    st.mrow[nb] = mc;
+    st.lsum[nb] *= alpha;
+#pragma unroll
+    for (int mb = 0; mb < D / 16; ++mb) st.O[nb][mb] *= alpha;
+  }
+}
+
+// A half tile's probabilities against the running max and their sums per kept
+// block.
+template <int D>
+__device__ __forceinline__ void probs_half(const FuseState<D> &st, const f32x4 (&acc)[2][2], float tc,
+                                           float (&pr)[2][2][4], float (&part)[2]) {
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    part[nb] = 0.f;
 #pragma unroll
     for (int d2 = 0; d2 < 2; ++d2)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         pr[nb][d2][i] = fast_exp2(fmaf(acc[nb][d2][i], tc, -st.mrow[nb]));
-        part += pr[nb][d2][i];
+        part[nb] += pr[nb][d2][i];
       }
-    st.lsum[nb] += part;
+  }
+}
+
+// Online softmax of one half tile: probabilities against the running max, the
+// denominators, and the bf16 B operands of O^T (with VFP32, also the low
+// parts).  The max is raised first where some logit is far above it; with the
+// lane's largest logits at hand (MX: half_max) they tell, else the sums of the
+// probabilities do, which are then taken again.
+template <int D, bool VFP32, bool MX>
+__device__ __forceinline__ void softmax_half(FuseState<D> &st, const f32x4 (&acc)[2][2], const float (&mx)[2],
+                                             float tc, bf16x8 (&ph)[2], bf16x8 (&pl)[2]) {
+  if (MX && __builtin_amdgcn_ballot_w64(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]) > kGrowBits) != 0)
+    raise_max<D>(st, mx);
+  float pr[2][2][4], part[2];
+  probs_half<D>(st, acc, tc, pr, part);
+  if (!MX && __builtin_amdgcn_ballot_w64(!(part[0] <= kGrowSum && part[1] <= kGrowSum)) != 0) {
+    float m[2];
+    half_max(acc, tc, m);
+    raise_max<D>(st, m);
+    probs_half<D>(st, acc, tc, pr, part);
   }
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
+    st.lsum[nb] += part[nb];
     const float *p0 = pr[nb][0], *p1 = pr[nb][1];
     const u32x4 hi = {pack_bf16(p0[0], p0[1]), pack_bf16(p0[2], p0[3]), pack_bf16(p1[0], p1[1]),
                       pack_bf16(p1[2], p1[3])};
@@ -242,31 +265,62 @@ __device__ __forceinline__ void values_half(FuseState<D> &st, const uint16_t *vt
   }
 }
 
-// One 64-row dropped tile (nd valid rows).  A wave whose every logit of a
-// half lies more than kSkipBits below its row's running max passes over the
-// half (vc_internal.h), unless `hold` (uniform) keeps every row.
+// One full 64-row dropped tile.
+template <int D, bool VFP32>
+__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, float tc, int lr, int lg) {
+  f32x4 accA[2][2], accB[2][2];
+  bf16x8 phA[2], plA[2], phB[2], plB[2];
+  const float none[2] = {};
+  scores_half<D>(st, vt, 0, lr, lg, accA);
+  scores_half<D>(st, vt, 1, lr, lg, accB);
+  softmax_half<D, VFP32, false>(st, accA, none, tc, phA, plA);
+  values_half<D, VFP32>(st, vt, 0, lr, lg, phA, plA);
+  softmax_half<D, VFP32, false>(st, accB, none, tc, phB, plB);
+  values_half<D, VFP32>(st, vt, 1, lr, lg, phB, plB);
+}
+
+// The same, but a wave whose every logit of a half lies more than kSkipBits
+// below its row's running max passes over the half (vc_internal.h), unless
+// hold is +inf (else -inf).  MASK: rows at or past nd are not dropped rows.
+// Also takes the squares of the next tile's values, which are on their way to
+// LDS (nx), beside the score products.  Returns the halves passed over
+// (uniform).
 template <int D, bool VFP32, bool MASK>
-__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, bool hold, int nd, float tc, int lr,
-                                          int lg) {
+__device__ __forceinline__ int fuse_tile_far(FuseState<D> &st, const uint16_t *vt, const DropRegs<D> &nx, float &sq, float hold, int nd, float tc,
+                                             int lr, int lg) {
   f32x4 accA[2][2], accB[2][2];
   bf16x8 phA[2], plA[2], phB[2], plB[2];
   float mxA[2], mxB[2];
   scores_half<D>(st, vt, 0, lr, lg, accA);
   scores_half<D>(st, vt, 1, lr, lg, accB);
-  half_max<MASK>(accA, 0, nd, tc, lg, mxA);
-  half_max<MASK>(accB, 1, nd, tc, lg, mxB);
-  auto far = [&](const float (&mx)[2]) {  // wave-uniform
-    return !hold && __builtin_amdgcn_ballot_w64(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]) > -kSkipBits) == 0;
+  sq = nx.squares();
+  if (MASK) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = 16 * d2 + 4 * lg + i;
+          if (row >= nd) accA[nb][d2][i] = kNegInf;
+          if (row + 32 >= nd) accB[nb][d2][i] = kNegInf;
+        }
+  }
+  half_max(accA, tc, mxA);
+  half_max(accB, tc, mxB);
+  auto far = [&](const float (&mx)[2]) {
+    return __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(mx[0] - st.mrow[0], mx[1] - st.mrow[1]), hold) > -kSkipBits) == 0;
   };
   const bool fa = far(mxA), fb = far(mxB);
   if (!fa) {
-    softmax_half<D, VFP32>(st, accA, mxA, tc, phA, plA);
+    softmax_half<D, VFP32, true>(st, accA, mxA, tc, phA, plA);
     values_half<D, VFP32>(st, vt, 0, lr, lg, phA, plA);
   }
   if (!fb) {
-    softmax_half<D, VFP32>(st, accB, mxB, tc, phB, plB);
+    softmax_half<D, VFP32, true>(st, accB, mxB, tc, phB, plB);
     values_half<D, VFP32>(st, vt, 1, lr, lg, phB, plB);
   }
+  return (int)fa + (int)fb;
 }
 
 // Workgroup = (fusion unit, 128 kept rows); wave w owns kept rows
@@ -281,7 +335,7 @@ using DropTiles = uint16_t[2][kDropTile * kPitchRow<D>];
 // starts fetching the next job's record while this one blends and stores).
 template <int D, bool VFP32, typename Next>
 __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[4], int tile, int start, DropTiles<D> &vr,
-                                         int (&s_hold)[2], Next &&next) {
+                                         float (&s_hold)[2], int &s_far, Next &&next) {
   constexpr int KS = D / 32, MB = D / 16, NB = 2;
   constexpr uint32_t kRowBytes = D * 2;
   const uint64_t Kin = uni64(rec[0].x, rec[0].y), Vin = uni64(rec[0].z, rec[0].w);
@@ -371,19 +425,21 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   }
   // The previous job's waves may still read their kept values from the
   // tile buffers (below): nothing is staged before every wave is past them.
-  if (tid < 2) s_hold[tid] = 0;
+  if (tid < 2) s_hold[tid] = kNegInf;
+  if (tid == 2) s_far = 0;
   __syncthreads();
-  // From the first tile with a too large value on, no tile is passed over.  A
+  // From the first tile with a too large value on (or one that is not a
+  // number), no tile is passed over.  A
   // staged tile's word belongs to its buffer: it is written before the barrier
   // that the tile's readers are past and again only after the next, so every
   // wave, and every run, decides alike.
-  bool hold = false;
-  auto check = [&](const Regs &set, int buf) {
-    if (__builtin_amdgcn_ballot_w64(set.large(p.skip_sq)) != 0) s_hold[buf] = 1;
+  bool test = nfull >= kFarTiles;
+  auto check = [&](float sq, int buf) {
+    if (__builtin_amdgcn_ballot_w64(!(sq < p.skip_sq)) != 0) s_hold[buf] = -kNegInf;
   };
   if (ntiles > 0) {
     set0.store(vr[0], row0, chunk);
-    check(set0, 0);
+    if (test) check(set0.squares(), 0);
     int rr[kIt];
     clamp_rows(di[2], rr);
     set0.load(Vin, rr, chunk);
@@ -420,11 +476,11 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   // End of tile t (parity PAR): stage tile t+1 from its register set into
   // the other LDS buffer, refill that set with tile t+3, fetch indices of
   // tile t+4, and synchronise.
-  auto advance = [&](auto par, int t) {
+  auto advance = [&](auto par, auto far, float sq, int t) {
     constexpr int PAR = decltype(par)::value;
     Regs &nx = PAR ? set0 : set1;
     nx.store(vr[PAR ^ 1], row0, chunk);
-    check(nx, PAR ^ 1);
+    if (decltype(far)::value) check(sq, PAR ^ 1);
     int nxt[kIt], rr[kIt];
     raw_idx(t + 4, nxt);
     clamp_rows(pend, rr);
@@ -435,25 +491,32 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   };
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
-  auto tile_of = [&](auto mask, int buf, int nd) {
-    hold |= uni((uint32_t)s_hold[buf]) != 0;
-    fuse_tile<D, VFP32, decltype(mask)::value>(st, vr[buf], hold, nd, tc, lr, lg);
-  };
+  float sq;
   int t = 0;
+  // Pairs of tiles with a look for halves to pass over, then without.
+  while (test && t + 1 < nfull) {
+    const float h0 = s_hold[0];
+    int far = fuse_tile_far<D, VFP32, false>(st, vr[0], set1, sq, h0, kDropTile, tc, lr, lg);
+    const int before = (int)uni((uint32_t)s_far);  // passed over in the tiles before t, all waves
+    advance(P0{}, std::true_type{}, sq, t);
+    const float h1 = fmaxf(h0, s_hold[1]);
+    far += fuse_tile_far<D, VFP32, false>(st, vr[1], set0, sq, h1, kDropTile, tc, lr, lg);
+    if (lane == 0 && far) atomicAdd(&s_far, far);
+    test = (int)uni(__float_as_uint(h1)) < 0 && before + kFarStart > kFarEach * t;
+    advance(P1{}, std::true_type{}, sq, t + 1);
+    t += 2;
+  }
   for (; t + 1 < nfull; t += 2) {
-    tile_of(std::false_type{}, 0, kDropTile);
-    advance(P0{}, t);
-    tile_of(std::false_type{}, 1, kDropTile);
-    advance(P1{}, t + 1);
+    fuse_tile<D, VFP32>(st, vr[0], tc, lr, lg);
+    advance(P0{}, std::false_type{}, 0.f, t);
+    fuse_tile<D, VFP32>(st, vr[1], tc, lr, lg);
+    advance(P1{}, std::false_type{}, 0.f, t + 1);
   }
-  if (t < nfull) {
-    tile_of(std::false_type{}, 0, kDropTile);
-    advance(P0{}, t);
-    ++t;
-  }
-  if (t < ntiles) {  // partial last tile
-    const int nd = r - t * kDropTile;
-    tile_of(std::true_type{}, t & 1, nd);
+  float hold = test ? kNegInf : -kNegInf;
+  while (t < ntiles) {  // an odd full tile and the partial one
+    hold = fmaxf(hold, s_hold[t & 1]);
+    fuse_tile_far<D, VFP32, true>(st, vr[t & 1], set1, sq, hold, r - t * kDropTile, tc, lr, lg);
+    if (++t < ntiles) advance(P0{}, std::true_type{}, sq, t - 1);
   }
   next();
 
@@ -513,7 +576,8 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
 template <int D, bool VFP32>
 __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
   __shared__ __attribute__((aligned(16))) DropTiles<D> vr;
-  __shared__ int s_hold[2];
+  __shared__ float s_hold[2];
+  __shared__ int s_far;
   __shared__ int s_code;
   const int x = (int)(blockIdx.x % kXcds);
   const int q0 = ldg(p.fwoff + x), qlen = ldg(p.fwoff + x + 1) - q0;
@@ -541,7 +605,7 @@ __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
     int ncode = -1;
     u32x4 nrec[4] = {};
     int nstart = 0;
-    fuse_job<D, VFP32>(p, rec, code & 255, (int)uni((uint32_t)start), vr, s_hold, [&]() {
+    fuse_job<D, VFP32>(p, rec, code & 255, (int)uni((uint32_t)start), vr, s_hold, s_far, [&]() {
       ncode = take();
       if (ncode >= 0) fetch(ncode, nrec, nstart);
     });

@@ -38,7 +38,7 @@ constexpr int kXcdsHost = 8;      // MI355X accelerator dies (host-side grid pla
 // out while every square of a dropped value is below
 //   skip_sq = 2^(kSkipBits - 39) kSkipBits ln 2 tau / (2 sqrt(d)) mu / (1 - mu)
 // (with tau = 1, mu = 0.7, d = 128: |V_d| up to 720; 48 bits would allow 42).
-// Larger values, and such that are not finite, keep every row.
+// From the first larger value on, or one that is not finite, every row is kept.
 constexpr int kSkipBits = 56;
 inline float fuse_skip_sq(double tau, double mu, int d) {
   const double margin = (double)(int64_t(1) << (kSkipBits - 39));

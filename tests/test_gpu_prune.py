@@ -284,6 +284,58 @@ def test_fusion_passes_over_far_tiles(dev, orc, d, values):
             assert np.abs(got - ref).max() <= bound, (n, l, np.abs(got - ref).max(), bound)
 
 
+@pytest.mark.parametrize("d,vfp32", [(64, True), (128, True), (128, False)])
+@pytest.mark.parametrize("values", ["frames", "flat", "flat then frames", "one frame far"])
+def test_fusion_looks_for_far_tiles_while_it_finds_some(dev, orc, d, vfp32, values):
+    """Lists of many dropped tiles, where a job stops looking for halves to pass
+    over (values without frames), goes on (in frames), or does either by where
+    its kept rows lie; several sequences of odd lengths and kv heads, each job
+    with a start of its own.  Bounds as in test_fusion_passes_over_far_tiles;
+    bf16 output: the weights are bf16, within 2^-9 of themselves, and so is the
+    result."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    from synthgen.device import to_host_bf16
+    gen = torch.Generator(device=dev).manual_seed(11)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev)
+    ns, Hkv, L, tpf = [1501, 3, 2403, 900], 2, 2, 48
+    params = vc.make_params(0.4, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, drop_all=True, v_out_fp32=vfp32)
+    K, V, Q = [], [], []
+    for l in range(L):
+        vs = []
+        for n in ns:
+            t = torch.arange(n, device=dev)
+            v = 0.8 * rnd(Hkv, n // tpf + 1, d)[:, t // tpf] + 0.6 * rnd(Hkv, n, d)
+            if values == "flat":
+                v = 0.3 * rnd(Hkv, n, d)
+            if values == "flat then frames":
+                v[:, : n // 2] = 0.3 * rnd(Hkv, n // 2, d)
+            if values == "one frame far":
+                v = 0.3 * rnd(Hkv, n, d)
+                v[:, n // 3:n // 3 + 64] = 4.0 * rnd(Hkv, 1, d)
+            vs.append(v.bfloat16().view(-1, d))
+        V.append(torch.cat(vs))
+        K.append(rnd(Hkv * sum(ns), d).bfloat16())
+        Q.append(rnd(len(ns), Hkv, 4, d))
+    pc = PruneCall(len(ns), L, Hkv, Hkv, d, 4, ns, params, K, V, Q, with_drop=True)
+    pc.run()
+    torch.cuda.synchronize()
+    for l in range(L):
+        for b, n in enumerate(ns):
+            for g in range(Hkv):
+                a0, a1 = pc.unit_rows(l, b, g)
+                d0, d1 = pc.unit_drop_rows(l, b, g)
+                kept, drop = pc.idx_out[l][a0:a1].cpu().numpy(), pc.drop_out[l][d0:d1].cpu().numpy()
+                r0 = sum(ns[:b]) * Hkv + g * n
+                Vu = V[l][r0:r0 + n]
+                ref = orc.fuse(to_host_bf16(Vu), kept, drop, 1.0, 0.7)
+                got = pc.v_out[l][a0:a1].float().cpu().numpy().astype(np.float64)
+                big = np.abs(Vu.float().cpu().numpy()[drop]).max() if len(drop) else 0.0
+                bound = (0.3 * 2.0 ** -17 * big + 4e-6 * np.abs(ref).max() if vfp32 else
+                         0.3 * 2.0 ** -8 * big + 2.0 ** -8 * np.abs(ref).max())
+                assert np.abs(got - ref).max() <= bound, (l, b, g, np.abs(got - ref).max(), bound)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("near,far,mu", [(6.0, 2.0 ** 40, 0.7), (8.0, 2.0 ** 100, 0.7), (6.0, 2.0 ** 40, 0.0),
                                          (6.0, 2.0 ** 7, 0.7), (6.0, 2.0 ** -40, 1.0)])
