@@ -578,36 +578,37 @@ __global__ __launch_bounds__(256, 2) void k_fuse(PrunePlan p) {
   __shared__ __attribute__((aligned(16))) DropTiles<D> vr;
   __shared__ float s_hold[2];
   __shared__ int s_far;
-  __shared__ int s_code;
+  __shared__ int s_code, s_start;
   const int x = (int)(blockIdx.x % kXcds);
   const int q0 = ldg(p.fwoff + x), qlen = ldg(p.fwoff + x + 1) - q0;
-  auto take = [&]() -> int {
+  auto take = [&](int &start) -> int {
     __syncthreads();  // every thread has read the previous code
     if (threadIdx.x == 0) {
       const int i = __hip_atomic_fetch_add(p.fcnt + x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       s_code = i < qlen ? ldg(p.fwjob + q0 + i) : -1;
+      s_start = i < qlen ? ldg(p.jstart + q0 + i) : 0;
     }
     __syncthreads();
+    start = s_start;
     return s_code;
   };
-  auto fetch = [&](int code, u32x4 (&rec)[4], int &start) {
-    start = ldg(p.jstart + (int64_t)(code >> 8) * p.njm + (code & 255));
+  auto fetch = [&](int code, u32x4 (&rec)[4]) {
     const u32x4 *rp = reinterpret_cast<const u32x4 *>(p.funit + (code >> 8));
 #pragma unroll
     for (int i = 0; i < 4; ++i) rec[i] = ld16(rp + i);
   };
   const int first = (int)(blockIdx.x / kXcds);
   int code = first < qlen ? ldg(p.fwjob + q0 + first) : -1;
+  int start = first < qlen ? ldg(p.jstart + q0 + first) : 0;
   u32x4 rec[4] = {};
-  int start = 0;
-  if (code >= 0) fetch(code, rec, start);
+  if (code >= 0) fetch(code, rec);
   while (code >= 0) {
     int ncode = -1;
     u32x4 nrec[4] = {};
     int nstart = 0;
     fuse_job<D, VFP32>(p, rec, code & 255, (int)uni((uint32_t)start), vr, s_hold, s_far, [&]() {
-      ncode = take();
-      if (ncode >= 0) fetch(ncode, nrec, nstart);
+      ncode = take(nstart);
+      if (ncode >= 0) fetch(ncode, nrec);
     });
     code = ncode;
     start = nstart;

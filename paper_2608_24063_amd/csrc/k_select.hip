@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void k_select(PrunePlan p) {
   const int k = ldg(p.kk + b * p.L + l);
   const int64_t toff = ldg(p.toff + b);
   const uint64_t idx_base = ldg(p.lp + LP_IDX * p.L + l), drop_base = ldg(p.lp + LP_DROP * p.L + l);
-  const int64_t jb = (int64_t)ldg(p.frank + u) * p.njm;  // (not used without kept tokens)
+  const int job = ldg(&p.funit[max(min(u, p.nfrec - 1), 0)].job);  // (not used without kept tokens)
   const int64_t orow = ldg(p.orow + l * (p.B + 1) + b), drow = ldg(p.drow + l * (p.B + 1) + b);
   const int r = nsv - k;
 
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kThreads) void k_select(PrunePlan p) {
         if (pk < (uint32_t)k) {
           stg(idx + pk, (int32_t)(v0 + i));
           // The first kept token of a fusion job: dropped tokens before it.
-          if (pk % kFuseRows == 0) stg(p.jstart + jb + pk / kFuseRows, (int32_t)pd);
+          if (pk % kFuseRows == 0) stg(p.jstart + job + pk / kFuseRows, (int32_t)pd);
         }
         ++pk;
       } else if (sv) {

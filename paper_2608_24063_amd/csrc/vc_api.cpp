@@ -30,13 +30,13 @@ struct Layout {
   std::vector<int32_t> fwoff, fwjob;   // fusion job queues per XCD (CSR): job = rank << 8 | tile
   std::vector<int32_t> fcnt0;          // jobs of each queue handed out at launch
   int32_t nfwg = 0;                    // persistent fusion workgroups
-  std::vector<int32_t> frank;          // rank of each (layer, sequence, kv head) among the fusion units
-  int32_t njm = 1;                     // most jobs of a fusion unit
+  std::vector<int32_t> ujob;           // first job, as in fwjob, of each (layer, sequence, kv head) up to the
+                                       // last with kept rows
   std::vector<int64_t> toff, orow, drow;
   // workspace regions (byte offsets)
   size_t off_plan, plan_bytes, off_qbf, off_part, off_S, off_gs, off_jstart, off_drop, total;
   // offsets inside the plan blob
-  size_t p_lp, p_nb, p_toff, p_kk, p_ns, p_orow, p_drow, p_funit, p_fwoff, p_fwjob, p_fcnt, p_frank;
+  size_t p_lp, p_nb, p_toff, p_kk, p_ns, p_orow, p_drow, p_funit, p_fwoff, p_fwjob, p_fcnt;
 };
 
 vc_status check_shape(const vc_shape *s) {
@@ -203,10 +203,6 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
       for (int32_t t = 0; t < nj; ++t) xj[x].push_back({cost, (int32_t)(rk << 8) | t});
       njobs += nj;
     }
-    y.frank.assign((size_t)y.h * y.B * y.Hkv, -1);
-    for (size_t rk = 0; rk < y.funit.size(); ++rk) y.frank[(size_t)y.funit[rk]] = (int32_t)rk;
-    y.njm = 1;
-    for (int32_t kk : y.k) y.njm = std::max(y.njm, (kk + kFuseRows - 1) / kFuseRows);
     y.fwoff.assign(kXcdsHost + 1, 0);
     y.fwjob.clear();
     y.fwjob.reserve((size_t)njobs);
@@ -219,6 +215,15 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
       for (const Job &j : jl) y.fwjob.push_back(j.code);
       y.fwoff[(size_t)x + 1] = (int32_t)y.fwjob.size();
       longest = std::max(longest, jl.size());
+    }
+    // A unit's jobs stand together, in the order of their rows: they were pushed
+    // so, cost the same, and the sort is stable.
+    y.ujob.clear();
+    for (size_t i = 0; i < y.fwjob.size(); ++i) {
+      if (y.fwjob[i] & 255) continue;
+      const size_t u = (size_t)y.funit[(size_t)(y.fwjob[i] >> 8)];
+      if (u >= y.ujob.size()) y.ujob.resize(u + 1, 0);
+      y.ujob[u] = (int32_t)i;
     }
     y.nfwg = (int32_t)std::min<int64_t>(kFuseSlots / kXcdsHost, (int64_t)longest) * kXcdsHost;
     // Jobs already handed out per queue: each of the XCD's workgroups starts
@@ -241,11 +246,10 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
   y.p_kk = o; o += sizeof(int32_t) * y.B * y.L;
   y.p_ns = o; o += sizeof(int32_t) * y.B * y.L;
   o = (o + 15) & ~size_t(15);
-  y.p_funit = o; o += sizeof(FuseUnit) * y.funit.size();
+  y.p_funit = o; o += sizeof(FuseUnit) * std::max(y.funit.size(), y.ujob.size());
   y.p_fwoff = o; o += sizeof(int32_t) * y.fwoff.size();
   y.p_fcnt = o; o += sizeof(int32_t) * kXcdsHost;  // queue counters, reset by every plan upload
   y.p_fwjob = o; o += sizeof(int32_t) * y.fwjob.size();
-  y.p_frank = o; o += sizeof(int32_t) * y.frank.size();
   o = (o + 7) & ~size_t(7);
   y.plan_bytes = o;
 
@@ -258,7 +262,7 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
                               : sizeof(float2) * (size_t)units * y.nks * y.R));
   y.off_S = w; w = align_up(w + sizeof(float) * (size_t)y.Ls * y.Ntot * y.Hkv);
   y.off_gs = w; w = align_up(w + (y.mode == VC_RANK_GLOBAL ? sizeof(float) * (size_t)y.Ntot : 0));
-  y.off_jstart = w; w = align_up(w + sizeof(int32_t) * y.funit.size() * (size_t)y.njm);
+  y.off_jstart = w; w = align_up(w + sizeof(int32_t) * y.fwjob.size());
   y.off_drop = w;
   for (int32_t l = 0; l < y.h; ++l) w = align_up(w + sizeof(int32_t) * (size_t)y.drow[(size_t)l * (y.B + 1) + y.B]);
   y.total = std::max<size_t>(w, kAlign);
@@ -431,7 +435,6 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   std::memcpy(blob.data() + y.p_fwoff, y.fwoff.data(), sizeof(int32_t) * y.fwoff.size());
   std::memcpy(blob.data() + y.p_fcnt, y.fcnt0.data(), sizeof(int32_t) * y.fcnt0.size());
   if (!y.fwjob.empty()) std::memcpy(blob.data() + y.p_fwjob, y.fwjob.data(), sizeof(int32_t) * y.fwjob.size());
-  if (!y.frank.empty()) std::memcpy(blob.data() + y.p_frank, y.frank.data(), sizeof(int32_t) * y.frank.size());
   {
     // Fusion unit records: absolute row addresses, so the fusion kernel
     // needs one dependent load before its index loads.
@@ -457,6 +460,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
       f.n = nn;
       fr[i] = f;
     }
+    for (size_t u = 0; u < y.ujob.size(); ++u) fr[u].job = y.ujob[u];
   }
 
   PrunePlan pl{};
@@ -466,6 +470,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   pl.pwg = y.pwg;
   pl.pring = y.pring;
   pl.nfunits = (int32_t)y.funit.size();
+  pl.nfrec = (int32_t)std::max(y.funit.size(), y.ujob.size());
   pl.nfwg = y.nfwg;
   pl.sc = (float)(1.4426950408889634 / std::sqrt((double)y.d));
   pl.tc = (float)(1.4426950408889634 / (double)params->tau);
@@ -487,9 +492,7 @@ vc_status viscache_prune_staged(const vc_shape *shape, const vc_params *params, 
   pl.fwoff = reinterpret_cast<const int32_t *>(pb + y.p_fwoff);
   pl.fwjob = reinterpret_cast<const int32_t *>(pb + y.p_fwjob);
   pl.fcnt = reinterpret_cast<int32_t *>(pb + y.p_fcnt);
-  pl.frank = reinterpret_cast<const int32_t *>(pb + y.p_frank);
   pl.jstart = reinterpret_cast<int32_t *>(ws + y.off_jstart);
-  pl.njm = y.njm;
   pl.qbf = reinterpret_cast<uint16_t *>(ws + y.off_qbf);
   pl.part = reinterpret_cast<float2 *>(ws + y.off_part);
   pl.pcol = reinterpret_cast<float *>(ws + y.off_part);

@@ -53,7 +53,9 @@ struct FuseUnit {
   uint64_t k_in, v_in;     // bf16 [n][d] input keys / values of the unit
   uint64_t k_out, v_out;   // bf16 [k][d] pruned keys; bf16 or fp32 [k][d] fused values
   uint64_t kept, drop;     // int32 [k] kept / [r] dropped token indices
-  int32_t k, r, n, pad;
+  int32_t k, r, n;
+  int32_t job;             // of the unit whose number is the record's: its first job (the record's
+                           // other members are those of the unit with this rank)
 };
 static_assert(sizeof(FuseUnit) == 64, "fusion unit record is four 16-byte words");
 
@@ -80,6 +82,7 @@ struct PrunePlan {
   int32_t nqg, nks;   // stats grid: query groups x key splits per unit
   int32_t ncol;       // column-sum chunks per unit (max over sequences)
   int32_t nfunits;    // units with kept rows
+  int32_t nfrec;      // records of funit: also up to the last unit number with kept rows
   int32_t nfwg;       // fusion workgroups (persistent; a multiple of 8, the same number per XCD)
   int32_t nmax;       // max n_b
   int32_t pwg;        // prefill: workgroups per unit (each owns every pwg-th 256-row group)
@@ -97,12 +100,10 @@ struct PrunePlan {
   const int32_t *ns;    // [B*L] survivors per (b, l)
   const int64_t *orow;  // [L*(B+1)] output row offsets per layer
   const int64_t *drow;  // [L*(B+1)] dropped-row offsets per layer
-  const FuseUnit *funit; // [nfunits] fusion units, most dropped rows first
+  const FuseUnit *funit; // fusion units by rank, most dropped rows first; word `job` by unit number
   const int32_t *fwoff;  // [9] job queue offsets per XCD
   const int32_t *fwjob;  // fusion jobs: unit rank << 8 | 128-row tile, each queue longest first
-  const int32_t *frank;  // [h*B*Hkv] rank of a unit among the fusion units (-1: none)
-  int32_t *jstart;       // [nfunits][njm] dropped rows before a fusion job's first kept row (selection)
-  int32_t njm;           // most fusion jobs of a unit
+  int32_t *jstart;       // per job, as in fwjob: dropped rows before its first kept row (from selection)
   int32_t *fcnt;         // [8] jobs handed out per queue (reset by every plan upload)
   uint16_t *qbf;        // [Ls][B][Hq][W][d] window queries in bf16
   float2 *part;         // [U][nks][R] partial row statistics (max*sc, sum)

@@ -99,6 +99,23 @@ def test_workspace_sizes(vc, sg):
     assert vc.viscache_decode_workspace_bytes(ds, 4000) >= 28 * 4 * 16 * 128 * 4
 
 
+def test_workspace_of_ragged_batches(vc):
+    """One long sequence among many short ones: the workspace is what the
+    sequences need (bf16 queries, row statistics, scores, dropped lists, the
+    plan's records and jobs), not the longest one's need times their number."""
+    L, Hkv, d, ns = 28, 8, 64, [32000] + [3] * 499
+    B = len(ns)
+    shape = vc.make_shape(B, L, Hkv, Hkv, d, 1, ns)
+    params = vc.make_params(0.3)
+    k, nsv, h = vc.viscache_budget(shape, params)
+    units = h * B * Hkv
+    drops = sum(Hkv * (nsv[b * L + l] - k[b * L + l]) for b in range(B) for l in range(h))
+    jobs = sum(Hkv * -(-k[b * L + l] // 128) for b in range(B) for l in range(h))
+    need = units * (2 * d + 8 * 8 + 4 * max(ns) // B + 64 + 16) + h * Hkv * 4 * sum(ns) + 4 * drops + 8 * jobs
+    plan = 8 * (8 * L + B) + L * (B + 1) * (16 + 8) + 4 * B
+    assert vc.viscache_prune_workspace_bytes(shape, params) <= 1.02 * (need + plan) + 256 * (L + 8)
+
+
 @pytest.mark.parametrize("bad,status", [
     (dict(d=96), "VC_ERR_UNSUPPORTED"), (dict(Hq=7, Hkv=2), "VC_ERR_SHAPE"),
     (dict(n=[40000]), "VC_ERR_UNSUPPORTED"), (dict(n=[-1]), "VC_ERR_SHAPE"),

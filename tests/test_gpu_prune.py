@@ -375,6 +375,59 @@ def test_fusion_keeps_large_values_of_small_weight(dev, orc, d, near, far, mu, v
         assert (np.abs(got - ref) <= bound).all(), np.abs(got - ref).max(0)[[0, d - 1]]
 
 
+@pytest.mark.parametrize("ns", [[1501, 700, 1100], [900], [3, 0, 2000, 1], [1, 700, 2]])
+def test_selection_tells_each_job_its_place(dev, ns):
+    """The number of dropped tokens before each fusion job's first kept one
+    stands where the job is listed, over units of unlike sizes and units that
+    keep nothing.  (A wrong one costs only time, so results do not show it.)
+    The plan's records are found in the workspace by their kept lists'
+    addresses; the jobs follow the records, their places come before the
+    dropped lists at the workspace's end."""
+    import paper_2608_24063_amd as vc
+    from paper_2608_24063_amd.tensors import PruneCall
+    gen = torch.Generator(device=dev).manual_seed(len(ns))
+    rnd = lambda *s: torch.randn(s, generator=gen, device=dev)
+    L, Hkv, d, W, B = 4, 2, 64, 4, len(ns)
+    params = vc.make_params(0.3)
+    args = (B, L, Hkv, Hkv, d, W, ns, params, *[[rnd(Hkv * sum(ns), d).bfloat16() for _ in range(L)] for _ in "KV"],
+            [rnd(B, Hkv, W, d) for _ in range(L)])
+    pc, ref = PruneCall(*args), PruneCall(*args, with_drop=True)
+    pc.ws.fill_(0xAB)
+    pc.run()
+    ref.run()
+    torch.cuda.synchronize()
+    ws = pc.ws.cpu().numpy()
+    want = {}  # address of the unit's kept list -> places of its jobs
+    drops = [0] * pc.h
+    numbers = []
+    for l in range(pc.h):
+        assert torch.equal(pc.idx_out[l], ref.idx_out[l])
+        for b in range(B):
+            for g in range(Hkv):
+                a0, a1 = pc.unit_rows(l, b, g)
+                d0, d1 = ref.unit_drop_rows(l, b, g)
+                drops[l] += d1 - d0
+                if a1 > a0:
+                    numbers.append((l * B + b) * Hkv + g)
+                    first = pc.idx_out[l][a0:a1:128].cpu().numpy()
+                    want[pc.idx_out[l].data_ptr() + 4 * a0] = np.searchsorted(ref.drop_out[l][d0:d1].cpu().numpy(), first)
+    up = lambda x: (x + 255) // 256 * 256
+    words = ws[:len(ws) // 8 * 8].view(np.uint64)
+    kept_at = {int(np.flatnonzero(words == np.uint64(a))[-1]) * 8 - 32: a for a in want}
+    base = min(kept_at)
+    rank = {(at - base) // 64: a for at, a in kept_at.items()}
+    assert sorted(rank) == list(range(len(want)))
+    njobs = sum(len(x) for x in want.values())
+    jobs_at = base + 64 * max(len(want), max(numbers) + 1) + 4 * 9 + 4 * 8
+    jobs = ws[jobs_at:jobs_at + 4 * njobs].view(np.int32)
+    off_drop = len(ws) - sum(up(4 * x) for x in drops)
+    at = off_drop - up(4 * njobs)
+    start = ws[at:at + 4 * njobs].view(np.int32)
+    assert sorted(set(map(int, jobs))) == sorted(r << 8 | t for r, a in rank.items() for t in range(len(want[a])))
+    for j, s in zip(jobs, start):
+        assert s == want[rank[int(j) >> 8]][int(j) & 255]
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("vfp32", [True, False])
 def test_fusion_repeats_bitwise_around_large_values(dev, d, vfp32):
