@@ -127,18 +127,30 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
     // Key tiles go through a ring of three buffers, products ahead of the
     // softmax, from kRingTokens tokens on (a sequence counting by its share of
     // the (query, key) pairs); shorter ones through two, whose start and end
-    // cost less (the ring loads three tiles past each pass's end).  The call
-    // with the ring against two buffers (28 layers, 28 / 4 heads, d = 128):
-    // 6001 tokens 6742 / 7048 us, 3136 2000 / 2081, 2700 1737 / 1773, 2300
-    // 1383 / 1382, 1800 958 / 934, 1201 549 / 512.
-    constexpr double kRingTokens = 2304;
+    // cost less (the ring loads three tiles past each pass's end), and so do
+    // calls whose workgroups do not fill the resident slots, where a
+    // workgroup's own time counts.  The call's time with the ring over that
+    // with two buffers (28 layers and 28 / 4 heads, 64 / 8, 16 / 2, 32 / 32 with
+    // 16 layers), d = 128: 1201 tokens 1.06, 1.04, 1.06, 1.09; 1800 1.02, 1.01,
+    // 1.02, 0.97; 2300 1.00, 1.00, 1.00, 1.03; 2500 1.00, 1.00, 1.01, 1.00; 2600
+    // to 2800 0.98 to 1.00; 3136 0.96, 0.96, 0.96, 0.97; 4500 0.96.  d = 64 (28 / 4
+    // and 32 / 8 heads): 1201 1.00, 0.99; 1400 1.00; 1536 0.94; 1650 0.99; 2300
+    // 0.97; 3136 0.92.  One path serves a mixed batch: 6001 with three of 600
+    // 0.95; two of 4000 with six of 1000 0.98; 3000 with four of 1200 1.01 and
+    // with seven of 800 1.02 (both take two buffers).  Workgroups below the
+    // slots (4 layers, 8 / 2 heads, d = 64): 1800 tokens 1.01, 2300 1.03, 4500
+    // 1.04, two of 2300 1.06; above: two of 3136 0.98, 7000 1.03, 10000 0.89.
+    const double kRingTokens = y.d == 64 ? 1536 : 2560;
     double pairs = 0, weighted = 0;
+    int64_t wgs = 0;
     for (int32_t nb : y.n) {
       const double N = (double)nb + y.W;
       pairs += N * N;
       weighted += N * N * N;
+      wgs += nb == 0 ? 0 : std::min<int64_t>(y.pwg, ((int64_t)y.G * (nb + (int64_t)y.W) + kStatsRows - 1) / kStatsRows);
     }
-    y.pring = weighted >= kRingTokens * pairs;
+    wgs *= (int64_t)y.Ls * y.Hkv;
+    y.pring = weighted >= kRingTokens * pairs && wgs > kScoreSlots;
   }
   y.nqg = (int32_t)((rows + kStatsRows - 1) / kStatsRows);
   const int64_t base = std::max<int64_t>(1, units * y.nqg);

@@ -706,12 +706,14 @@ def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W, longest):
     ring of three tiles and the 256-row group (tiles without a mask, on the
     diagonal and past a wave's rows; row groups that straddle heads; tiles of
     visual and text keys).  A long sequence in the batch, which is not compared
-    itself, takes the others through the ring."""
+    itself, takes the others through the ring; so that there are workgroups
+    enough for it, the two layers' tensors then serve 24 layers."""
     import paper_2608_24063_amd as vc
     from paper_2608_24063_amd.tensors import PruneCall
     from synthgen.device import to_host_bf16
     gen = np.random.default_rng(G * 1000 + W)
-    params = vc.make_params(0.5, h=2, m=1.0, schedule=vc.VC_SCHED_FIXED, score_queries=vc.VC_SCORE_PREFILL)
+    L = 24 if longest else 2
+    params = vc.make_params(0.5, h=L, m=1.0, schedule=vc.VC_SCHED_FIXED, score_queries=vc.VC_SCORE_PREFILL)
     n = [1, 63, 64, 65, 191, 193, 256, 321, 449] + ([longest] if longest else [])
     B = len(n)
     mk = lambda *s: torch.from_numpy(gen.standard_normal(s).astype(np.float32)).to(dev)
@@ -719,7 +721,8 @@ def test_prefill_scores_over_row_and_tile_counts(dev, orc, d, G, W, longest):
     V = [mk(sum(n), d).to(torch.bfloat16) for _ in range(2)]
     T = [mk(B, 1, W, d).to(torch.bfloat16) for _ in range(2)]
     Q = [mk(G * (sum(n) + B * W), d).to(torch.bfloat16).float() for _ in range(2)]
-    pc = PruneCall(B, 2, G, 1, d, W, n, params, K, V, Q, k_text=T)
+    K, V, T, Q = (x * (L // 2) for x in (K, V, T, Q))
+    pc = PruneCall(B, L, G, 1, d, W, n, params, K, V, Q, k_text=T)
     pc.run()
     torch.cuda.synchronize()
     off, _ = vc.viscache_prune_score_offsets(pc.shape, params)
