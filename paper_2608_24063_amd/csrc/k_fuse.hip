@@ -37,7 +37,10 @@
 // without.  Fusion of eight sequences of 14k to 23k tokens (28 layers, 4 kv
 // heads, d = 128), in us: never looking 2480 with values in frames and without;
 // always 1980 and 2850; as it is 2030 and 2650.  12.5k tokens: 168 and 163;
-// 141 and 176; 143 and 170.  (Of the 2030, the score products take 500, at the
+// 141 and 176; 143 and 170.  With d = 64 the logits lie half as far apart and a
+// half saves half as much: 1420 and 1460 without, 1600 and 1530 with (four
+// sequences of 14k to 22k, 32 / 8 heads), so jobs of that kind do not look, and
+// walk their tiles in order: 1430.  (Of the 2030, the score products take 500, at the
 // matrix cores' rate, staging 350 and the jobs' row copies 770, at the rate of
 // a large copy; they overlap little.)  A job that could start to look again
 // gained nothing (2100 and 2700).
@@ -265,16 +268,29 @@ __device__ __forceinline__ void values_half(FuseState<D> &st, const uint16_t *vt
   }
 }
 
-// One full 64-row dropped tile.
-template <int D, bool VFP32>
-__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, float tc, int lr, int lg) {
+// Rows of a half tile (h) at or past nd get no weight.
+__device__ __forceinline__ void mask_half(f32x4 (&acc)[2][2], int h, int nd, int lg) {
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (32 * h + 16 * d2 + 4 * lg + i >= nd) acc[nb][d2][i] = kNegInf;
+}
+
+// One 64-row dropped tile.  MASK: rows at or past nd are not dropped rows.
+template <int D, bool VFP32, bool MASK>
+__device__ __forceinline__ void fuse_tile(FuseState<D> &st, const uint16_t *vt, int nd, float tc, int lr, int lg) {
   f32x4 accA[2][2], accB[2][2];
   bf16x8 phA[2], plA[2], phB[2], plB[2];
   const float none[2] = {};
   scores_half<D>(st, vt, 0, lr, lg, accA);
   scores_half<D>(st, vt, 1, lr, lg, accB);
+  if (MASK) mask_half(accA, 0, nd, lg);
   softmax_half<D, VFP32, false>(st, accA, none, tc, phA, plA);
   values_half<D, VFP32>(st, vt, 0, lr, lg, phA, plA);
+  if (MASK) mask_half(accB, 1, nd, lg);
   softmax_half<D, VFP32, false>(st, accB, none, tc, phB, plB);
   values_half<D, VFP32>(st, vt, 1, lr, lg, phB, plB);
 }
@@ -295,16 +311,8 @@ __device__ __forceinline__ int fuse_tile_far(FuseState<D> &st, const uint16_t *v
   scores_half<D>(st, vt, 1, lr, lg, accB);
   sq = nx.squares();
   if (MASK) {
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int d2 = 0; d2 < 2; ++d2)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * d2 + 4 * lg + i;
-          if (row >= nd) accA[nb][d2][i] = kNegInf;
-          if (row + 32 >= nd) accB[nb][d2][i] = kNegInf;
-        }
+    mask_half(accA, 0, nd, lg);
+    mask_half(accB, 1, nd, lg);
   }
   half_max(accA, tc, mxA);
   half_max(accB, tc, mxB);
@@ -375,7 +383,8 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   // far tiles can be passed over.  The full tiles rotate; the partial one
   // stays last.
   const int nfull = r / kDropTile;
-  const int t0 = min(max(start / kDropTile, 0), max(nfull - 1, 0));
+  constexpr bool kLook = D == 128;  // at d = 64 it did not pay (above)
+  const int t0 = kLook ? min(max(start / kDropTile, 0), max(nfull - 1, 0)) : 0;
   auto raw_idx = [&](int dt, int (&o)[kIt]) {
     const int s = min(dt, ntiles - 1), rot = s + t0 >= nfull ? s + t0 - nfull : s + t0;
     const int base = (s < nfull ? rot : s) * kDropTile + row0;
@@ -433,7 +442,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   // staged tile's word belongs to its buffer: it is written before the barrier
   // that the tile's readers are past and again only after the next, so every
   // wave, and every run, decides alike.
-  bool test = nfull >= kFarTiles;
+  bool test = kLook && nfull >= kFarTiles;
   auto check = [&](float sq, int buf) {
     if (__builtin_amdgcn_ballot_w64(!(sq < p.skip_sq)) != 0) s_hold[buf] = -kNegInf;
   };
@@ -494,7 +503,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
   float sq;
   int t = 0;
   // Pairs of tiles with a look for halves to pass over, then without.
-  while (test && t + 1 < nfull) {
+  while (kLook && test && t + 1 < nfull) {
     const float h0 = s_hold[0];
     int far = fuse_tile_far<D, VFP32, false>(st, vr[0], set1, sq, h0, kDropTile, tc, lr, lg);
     const int before = (int)uni((uint32_t)s_far);  // passed over in the tiles before t, all waves
@@ -507,16 +516,21 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
     t += 2;
   }
   for (; t + 1 < nfull; t += 2) {
-    fuse_tile<D, VFP32>(st, vr[0], tc, lr, lg);
+    fuse_tile<D, VFP32, false>(st, vr[0], kDropTile, tc, lr, lg);
     advance(P0{}, std::false_type{}, 0.f, t);
-    fuse_tile<D, VFP32>(st, vr[1], tc, lr, lg);
+    fuse_tile<D, VFP32, false>(st, vr[1], kDropTile, tc, lr, lg);
     advance(P1{}, std::false_type{}, 0.f, t + 1);
   }
   float hold = test ? kNegInf : -kNegInf;
   while (t < ntiles) {  // an odd full tile and the partial one
-    hold = fmaxf(hold, s_hold[t & 1]);
-    fuse_tile_far<D, VFP32, true>(st, vr[t & 1], set1, sq, hold, r - t * kDropTile, tc, lr, lg);
-    if (++t < ntiles) advance(P0{}, std::true_type{}, sq, t - 1);
+    const int nd = r - t * kDropTile;
+    if constexpr (kLook) {
+      hold = fmaxf(hold, s_hold[t & 1]);
+      fuse_tile_far<D, VFP32, true>(st, vr[t & 1], set1, sq, hold, nd, tc, lr, lg);
+    } else {
+      fuse_tile<D, VFP32, true>(st, vr[t & 1], nd, tc, lr, lg);
+    }
+    if (++t < ntiles) advance(P0{}, std::integral_constant<bool, kLook>{}, kLook ? sq : 0.f, t - 1);
   }
   next();
 
