@@ -80,7 +80,10 @@ def algorithmic(w, pc, n_list, prefill=False):
     the kept-key rows the gather reads again) are the implementation's, not
     the method's.  MFMA flops count the score contraction once and both
     fusion products; exps one per (window row, key) and per (kept, dropped)
-    pair."""
+    pair.  With d = 128 fusion leaves out the exponentials and the value
+    products of dropped rows that are far below a kept row's maximum, by the
+    data: its flops and exps there are those that no call leaves out (the
+    products V_k V_d), and flops_all counts every value product as well."""
     L, Hq, Hkv, d, W, G = w.L, w.Hq, w.Hkv, w.d, w.W, w.G
     R = G * W
     Ls = pc.h if pc.params.rank_mode == 0 else L
@@ -113,16 +116,17 @@ def algorithmic(w, pc, n_list, prefill=False):
                                    exps=0)
         k_bytes += t_bytes
         score_flops, score_exps = 2 * d * p_all, p_all
-    fb, fb_alg, ff, fe = 0, 0, 0, 0
+    fb, fb_alg, ff, fa, fe = 0, 0, 0, 0, 0
     for b, n in enumerate(n_list):
         for l in range(pc.h):
             k, ns = pc.k[b * L + l], pc.n_surv[b * L + l]
             r = ns - k
             fb_alg += Hkv * (ns * d * 2 + k * (2 * d * 2 + 4))
             fb += Hkv * (ns * d * 2 + k * d * 2 + k * (2 * d * 2 + 4))
-            ff += Hkv * 4 * k * r * d
-            fe += Hkv * k * r
-    out["gather_fuse"] = dict(bytes=fb, flops=ff, exps=fe)
+            ff += Hkv * (2 if d == 128 else 4) * k * r * d
+            fa += Hkv * 4 * k * r * d
+            fe += Hkv * k * r if d != 128 else 0
+    out["gather_fuse"] = dict(bytes=fb, flops=ff, exps=fe, flops_all=fa)
     out["select"] = dict(bytes=sum(Hkv * n * 4 for n in n_list) * pc.h, flops=0, exps=0)
     out["path_bytes"] = k_bytes + q_bytes + fb_alg          # B_alg
     out["path_bytes_kept_reread"] = k_bytes + q_bytes + fb  # plus the kept-key rows read again
@@ -346,7 +350,7 @@ def prune_report(w, pc, n, tot, stage, prefill, workload):
     kernels = PREFILL_STAGE_KERNEL if prefill else STAGE_KERNEL
     roof["traffic"] = stored_traffic(dom, workload, kernels)
     roof.update(kernel=kernels[dom][0], stage=dom, kernel_us=stage_us[dom], alg_flops=a["flops"],
-                alg_bytes=a["bytes"], hbm_frac=fr_hbm, mfma_frac=fr_mfma, exp_per_s=a["exps"] / td)
+                alg_flops_all=a.get("flops_all", a["flops"]), alg_bytes=a["bytes"], hbm_frac=fr_hbm, mfma_frac=fr_mfma, exp_per_s=a["exps"] / td)
     return dict(ms=ms, ms_mean=sum(tot) / len(tot), gbs_in=in_bytes / t / 1e9, in_bytes=in_bytes,
                 b_alg=alg["path_bytes"], hbm_gbs=alg["path_bytes"] / t / 1e9,
                 hbm_frac=alg["path_bytes"] / t / 1e9 / HBM_PEAK_GBS,
