@@ -476,7 +476,7 @@ __device__ __forceinline__ void fuse_job(const PrunePlan &p, const u32x4 (&rec)[
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) st.O[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
     // Running maxima are pre-multiplied by log2(e)/tau; the finite floor makes
-    // the first half tile raise them (its probabilities overflow the limit).
+    // the first half tile raise them.
     st.mrow[nb] = -1e30f;
     st.lsum[nb] = 0.f;
   }

@@ -350,11 +350,11 @@ __global__ __launch_bounds__(256, 2) void k_score_stats(PrunePlan p, uint32_t *p
           key_products<D>(a, bq[0], cur);
           // The first key split also leaves the bf16 queries for the column pass.
           if (ks == 0) {
-      #pragma unroll
+#pragma unroll
             for (int qb = 0; qb < NQ; ++qb) {
               const int row = row0 + qb * 16 + lr;
               if (row < p.R) {
-      #pragma unroll
+#pragma unroll
                 for (int s = 0; s < KS; ++s) st16(Qb + (int64_t)row * D + 32 * s + 8 * lg, as_u32x4(bq[qb][s]));
               }
             }

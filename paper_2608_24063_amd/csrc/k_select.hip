@@ -221,10 +221,13 @@ hipError_t launch_select(const PrunePlan &p, hipStream_t st) {
   if (grid == 0) return hipSuccess;
   // 256 threads hold up to 8 scores each, then 512 and 1024 threads up to 16,
   // then 1024 threads up to 32.  Fewer scores per thread shorten each radix
-  // pass, more waves lengthen the barriers and the scan: 512 threads beat both
-  // 256 and 1024 at 3136 keys (measured with a histogram per wave).
+  // pass; more waves lengthen the barriers and the scan, and leave fewer units
+  // room on a CU.  Stage times in us (84 units a sequence) with 256, 512 and
+  // 1024 threads: 512 keys 9.0, 10.2, 10.5; 1568 11.1, 11.2, 11.7; 2048 11.9,
+  // 11.5, 11.7; eight sequences of 1500 15.2, 17.0, 29.8; 3136 14.3, 12.9, 13.3;
+  // eight of 3136 20.8, 20.5, 33.4; 6000 (512, 1024) 16.3, 15.5; 8192 20.2, 19.2.
   if (p.nmax <= 256 * 8)
-    hipLaunchKernelGGL((k_select<256, 16>), dim3(grid), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((k_select<256, 8>), dim3(grid), dim3(256), 0, st, p);
   else if (p.nmax <= 512 * 16)
     hipLaunchKernelGGL((k_select<512, 16>), dim3(grid), dim3(512), 0, st, p);
   else if (p.nmax <= 1024 * 16)

@@ -192,7 +192,9 @@ vc_status make_layout(const vc_shape *s, const vc_params *p, Layout &y) {
   // to XCDs largest first, each to the XCD with the least work so far (all
   // jobs of a unit share its dropped rows in that XCD's L2); each queue lists
   // its jobs longest first.  Cost of a job: its dropped tiles plus a job's
-  // fixed start-up and wind-down, in tile units.  The persistent workgroups
+  // fixed start-up and wind-down, in tile units (tiles that the kernel passes
+  // over take less, by the data, which the host does not see; a start-up of 8
+  // or 12 tiles in place of 4 made no difference).  The persistent workgroups
   // of an XCD (block b runs on XCD b % 8) start on the first jobs of its
   // queue and take the rest one by one as they finish, so the work balances
   // itself at run time.
